@@ -197,10 +197,8 @@ cb_status cb_stats_accumulate(cb_plan *plan, const cb_cache *src, const cb_cache
  * bias row is penalized too); with CB_RIDGE_BIAS_UNPENALIZED the last
  * diagonal entry of D is 0, which equals the paper's centered weighted ridge
  * (weights rescaled to mean one).  G is read in full and must be symmetric
- * (cb_stats_accumulate writes it so).  Gauss-Jordan elimination without
- * pivoting in fp64, one workgroup per system; for the symmetric positive
- * definite G + lambda_m D its pivots are the squared diagonal of the Cholesky
- * factor.  info[m] = 0 on success, else the 1-based index of the first pivot
+ * (cb_stats_accumulate writes it so).  Blocked Cholesky in fp64, one
+ * workgroup per system.  info[m] = 0 on success, else the 1-based index of the first pivot
  * that is not positive and finite (the column where Cholesky would stop), and
  * maps[m] is zero-filled.  P in {65, 97, 129}, d_t in {64, 96, 128}; wider
  * systems return CB_ERR_UNSUPPORTED (use cb_ridge_solve_ws).
@@ -301,8 +299,8 @@ cb_status cb_stats_shift_finish(const cb_plan *plan, const double *shift, double
  * lambda, or with CB_LAMBDA_RELATIVE lambda * (tr A + S |mu_x|^2 + S) / (d_s + 1),
  * S = sum w: the relative lambda of cb_ridge_solve on the uncentered moments
  * of the same data, so both forms solve the same problem
- * (CB_RIDGE_BIAS_UNPENALIZED is accepted and changes nothing).  Gauss-Jordan
- * elimination in fp64, one workgroup per system.  info[m] = 0 on success, else
+ * (CB_RIDGE_BIAS_UNPENALIZED is accepted and changes nothing).  Blocked
+ * Cholesky in fp64, one workgroup per system.  info[m] = 0 on success, else
  * the 1-based index of the first pivot of A + lambda_m I that is not positive
  * and finite, and maps[m] is zero-filled.  d_s, d_t in {64, 96, 128}.
  */
