@@ -568,10 +568,11 @@ cb_status cb_plan_create_multi(const cb_head_map_multi *map, const cb_cache *src
  * workspace.  Otherwise (P <= 4097, d_t in {64, 96, 128}) each system is
  * factored in fp64 in `workspace` (device memory owned by the caller, 8-byte
  * aligned, at least cb_ridge_solve_workspace_bytes(P, d_t, 1) bytes): a
- * left-looking blocked Cholesky M = L L^T in 32-column panels, then the
- * forward and back substitutions for the d_t right-hand sides, one workgroup
- * of 256 threads per system; the systems are processed in batches of
- * workspace_bytes / cb_ridge_solve_workspace_bytes(P, d_t, 1).  info[m] = 0, or
+ * blocked Cholesky M = U^T U in panels of 128 rows that carries the d_t
+ * right-hand sides along, then the back substitution, a system's tiles spread
+ * over many workgroups; the systems are processed in batches of as many as
+ * the workspace holds (one for every cb_ridge_solve_workspace_bytes(P, d_t, 1)
+ * bytes, or more).  info[m] = 0, or
  * the 1-based column of the first pivot that is not positive and finite
  * (maps[m] zero-filled).  Errors: CB_ERR_SHAPE (workspace too small), else as
  * cb_ridge_solve.
@@ -590,8 +591,8 @@ int64_t cb_ridge_solve_workspace_bytes(int32_t P, int32_t d_t, int32_t n_systems
  * the workspace, same arithmetic, identical results -- with the factors in a
  * fixed device array of cb_ridge_solve_noalloc_max_bytes() bytes (128 MiB)
  * that every GPU the library runs on holds until the process ends.  The
- * systems are solved in batches of that size divided by
- * cb_ridge_solve_workspace_bytes(P, d_t, 1).  No call allocates; the first call
+ * systems are solved in batches of as many as it holds (22 at P = 1025, d_t =
+ * 128).  No call allocates; the first call
  * on a device looks up the array's address there (make it before a graph
  * capture).  The array keeps the last call's contents; calls that overlap on
  * one GPU (several streams or threads) race on it and must be serialized.

@@ -70,3 +70,56 @@ def test_narrow_solve_failing_pivots(cb, ds):
     assert (maps[:-1] == 0).all()
     W, _ = oracle.ridge_solve(G[-1:].astype(np.float64), C[-1:].astype(np.float64), 1e-3, relative=False)
     assert _relF(maps[-1].double().cpu().numpy(), W[0]) < 1e-6
+
+
+# The wide solver: the first width past the narrow one, panels that end ragged, one past a multiple of 128 (the bias
+# kept as a column of its own) and on it, one and two panels short of 1025; a workspace of exactly one system (every
+# system a batch of its own), one of two and a half, and the fixed scratch; all against the oracle.
+@pytest.mark.parametrize("P", [130, 144, 161, 200, 256, 257, 300, 385, 400, 1025])
+@pytest.mark.parametrize("dt", [64, 96, 128])
+def test_wide_solve_shapes(cb, P, dt):
+    import oracle
+    if P > 400 and dt != 128:
+        pytest.skip("one width is enough at this size")
+    n = 3
+    G, C = _moments(n, P, dt, P + dt)
+    # the middle system fails at P // 2 + 1: its diagonal there is -tr / P, past the ridge of tr / (100 P)
+    G[1, P // 2, P // 2] = -np.trace(G[1]) / P
+    W, io = oracle.ridge_solve(G.astype(np.float64), C.astype(np.float64), 1e-2, relative=True, bias_unpenalized=True)
+    assert io.tolist() == [0, P // 2 + 1, 0]
+    Gd, Cd = torch.from_numpy(G).cuda(), torch.from_numpy(C).cuda()
+    one = cb.cb_ridge_solve_workspace_bytes(P, dt, 1)
+    assert one == 8 * (P * P + P * dt)
+    for ws_bytes in (one, 2 * one + one // 2, None):
+        maps, info = torch.full_like(Cd, 7.0), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        if ws_bytes is None:
+            cb.cb_ridge_solve_noalloc(Gd, Cd, 1e-2, REL | UNPEN, maps, info)
+        else:
+            # exactly the bytes asked for, with guard values behind them
+            buf = torch.full((ws_bytes // 8 + 64,), 3.0, dtype=torch.float64, device="cuda")
+            cb.cb_ridge_solve_ws(Gd, Cd, 1e-2, REL | UNPEN, maps, info, buf[:ws_bytes // 8])
+            assert (buf[ws_bytes // 8:] == 3.0).all()
+        assert info.cpu().tolist() == io.tolist()
+        assert (maps[1] == 0).all()
+        for m in (0, 2):
+            assert _relF(maps[m].double().cpu().numpy(), W[m]) < 1e-6, (P, dt, ws_bytes, m)
+
+
+# Centered systems: a width that is a multiple of 128 (no bias column in the system) and one past it, whose last
+# feature takes the bias column's place.
+@pytest.mark.parametrize("dx", [256, 257, 330])
+def test_wide_solve_centered_shapes(cb, dx):
+    import oracle
+    n, dt = 2, 96
+    G, C = _moments(n, dx, dt, dx)
+    rng = np.random.default_rng(dx)
+    sums = np.concatenate([np.full((n, 1), 50.0), 20 * rng.standard_normal((n, dx + dt))], axis=1)
+    W, io = oracle.ridge_solve_centered(sums, G.astype(np.float64), C.astype(np.float64), 1e-3, relative=True)
+    ws = torch.empty(cb.cb_ridge_solve_workspace_bytes(dx, dt, n), dtype=torch.uint8, device="cuda")
+    maps = torch.full((n, dx + 1, dt), 7.0, device="cuda")
+    info = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cb.cb_ridge_solve_centered_ws(torch.from_numpy(sums).cuda(), torch.from_numpy(G).cuda(), torch.from_numpy(C).cuda(),
+                                  1e-3, REL, maps, info, ws)
+    assert (info.cpu().numpy() == 0).all() and (io == 0).all()
+    for m in range(n):
+        assert _relF(maps[m].double().cpu().numpy(), W[m]) < 1e-6
