@@ -11,87 +11,111 @@
 //     RSS = TSS - 2 tr(W^T B) + tr(W^T A W),      R^2 = 1 - RSS / TSS,
 // which needs no further pass over the tokens.
 //
-// probe_r2_kernel: one workgroup of 256 threads per map.  W and A are staged
-// in LDS (fp32; A with a padded row stride so that the 32 rows read by a wave
-// fall in different banks).  Thread (i, h) forms row i of A W over column
-// half h in fp32 and its share of both traces in fp64; the workgroup adds the
-// shares in a fixed order.
+// probe_r2_kernel: one workgroup per map, one wave per 32 rows of A W, formed
+// in fp32 by v_mfma_f32_32x32x2_f32.  A is symmetric, so the left operand's
+// column k is row k of A: both operands are rows, 32 consecutive floats per half
+// wave.  W is staged in LDS (every wave reads all of it); each element of A and B
+// is read once, from global memory, A a group of K steps ahead.  The traces and
+// TSS are summed in fp64 over the workgroup in a fixed order.
+// Bound: HBM, 196 KB per map at d_s = d_t = 128 (the fp32 products take 7 us of
+// a compute unit per map and overlap with the other map it holds).  Measured,
+// 10,240 maps of 128 and 128: 6.70 ms with FMAs from LDS, a thread per half row,
+// and one thread summing TSS; now 0.60 ms.
 #include "cb_internal.h"
 
 namespace cb {
 namespace {
 
-constexpr int kMaxD = 128;
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-__global__ __launch_bounds__(256) void probe_r2_kernel(int d_s, int d_t, const double *__restrict__ sums,
-                                                       const double *__restrict__ sq, const float *__restrict__ A,
-                                                       const float *__restrict__ B, const float *__restrict__ maps,
-                                                       double *__restrict__ r2) {
-    __shared__ __attribute__((aligned(16))) float Ws[kMaxD * kMaxD];       // W [d_s][d_t]
-    __shared__ float As[kMaxD * (kMaxD + 1)];                              // A [d_s][d_s + 1]
-    __shared__ double red[2][256 / 64];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const float *Am = A + (int64_t)m * d_s * d_s;
-    const float *Bm = B + (int64_t)m * d_s * d_t;
-    const float *Wm = maps + (int64_t)m * (d_s + 1) * d_t;                  // rows 0..d_s-1 = W
-    const double *sm = sums + (int64_t)m * (1 + d_s + d_t);
-    const double *qm = sq + (int64_t)m * (d_s + d_t);
-    for (int e = tid; e < d_s * d_t; e += 256) Ws[e] = Wm[e];
-    for (int e = tid; e < d_s * d_s; e += 256) As[(e / d_s) * (kMaxD + 1) + e % d_s] = Am[e];
+template <int DS, int DT>
+__global__ __launch_bounds__(2 * DS) void probe_r2_kernel(const double *__restrict__ sums,
+                                                          const double *__restrict__ sq, const float *__restrict__ A,
+                                                          const float *__restrict__ B, const float *__restrict__ maps,
+                                                          double *__restrict__ r2) {
+    constexpr int RB = DS / 32, CB = DT / 32, NT = 64 * RB;   // row blocks (waves), column blocks
+    constexpr int GK = 16;                                    // K steps (two rows of A) per group
+    static_assert(DS / 2 % GK == 0, "whole groups");
+    __shared__ __attribute__((aligned(16))) float Ws[DS * DT];   // W [d_s][d_t]
+    __shared__ double red[3][RB];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, h = lane >> 5;
+    const float *Am = A + (int64_t)m * DS * DS;
+    const float *Bm = B + (int64_t)m * DS * DT;
+    const float *Wm = maps + (int64_t)m * (DS + 1) * DT;      // rows 0..d_s-1 = W
+    const double *sm = sums + (int64_t)m * (1 + DS + DT);
+    const double *qm = sq + (int64_t)m * (DS + DT);
+
+    const float *Ap = Am + h * DS + 32 * wave + n;            // A[k][32 wave + n], k = 2 step + h
+    float a[2][GK];
+#pragma unroll
+    for (int s = 0; s < GK; ++s) a[0][s] = Ap[2 * s * DS];
+#pragma unroll
+    for (int e = 0; e < DS * DT / NT; ++e) Ws[e * NT + tid] = Wm[e * NT + tid];
     __syncthreads();
 
-    // row i of A W over the column half h (d_t / 2 consecutive columns)
-    const int i = tid >> 1, h = tid & 1, half = d_t / 2, j0 = h * half;
-    double t1 = 0.0, t2 = 0.0;                                             // tr(W^T B), tr(W^T A W) shares
-    if (i < d_s) {
-        float aw[kMaxD / 2];
+    f32x16_t acc[CB];
 #pragma unroll
-        for (int q = 0; q < kMaxD / 2; ++q) aw[q] = 0.f;
-        for (int k = 0; k < d_s; ++k) {
-            const float a = As[i * (kMaxD + 1) + k];
-            const float4 *wr = (const float4 *)(Ws + k * d_t + j0);
+    for (int c = 0; c < CB; ++c)
 #pragma unroll
-            for (int q4 = 0; q4 < kMaxD / 8; ++q4) {
-                if (4 * q4 < half) {
-                    const float4 w = wr[q4];
-                    aw[4 * q4] = __builtin_fmaf(a, w.x, aw[4 * q4]);
-                    aw[4 * q4 + 1] = __builtin_fmaf(a, w.y, aw[4 * q4 + 1]);
-                    aw[4 * q4 + 2] = __builtin_fmaf(a, w.z, aw[4 * q4 + 2]);
-                    aw[4 * q4 + 3] = __builtin_fmaf(a, w.w, aw[4 * q4 + 3]);
-                }
-            }
+        for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+#pragma unroll
+    for (int gk = 0; gk < DS / 2 / GK; ++gk) {
+        if (gk + 1 < DS / 2 / GK) {
+#pragma unroll
+            for (int s = 0; s < GK; ++s) a[(gk + 1) & 1][s] = Ap[2 * ((gk + 1) * GK + s) * DS];
         }
 #pragma unroll
-        for (int q = 0; q < kMaxD / 2; ++q) {
-            if (q < half) {
-                const double w = Ws[i * d_t + j0 + q];
-                t1 += w * (double)Bm[(int64_t)i * d_t + j0 + q];
-                t2 += w * (double)aw[q];
-            }
+        for (int s = 0; s < GK; ++s) {
+            const int k = 2 * (gk * GK + s) + h;
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[gk & 1][s], Ws[k * DT + 32 * c + n], acc[c], 0, 0, 0);
         }
     }
+    // shares of tr(W^T B) and tr(W^T A W); row of acc[c][v]: 8 (v / 4) + 4 h + v mod 4, column 32 c + n
+    double t1 = 0.0, t2 = 0.0, ts = 0.0;
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int e = (32 * wave + 8 * (v >> 2) + 4 * h + (v & 3)) * DT + 32 * c + n;
+            const double w = (double)Ws[e];
+            t1 = __builtin_fma(w, (double)Bm[e], t1);
+            t2 = __builtin_fma(w, (double)acc[c][v], t2);
+        }
+    const double S = sm[0];
+    for (int j = tid; j < DT; j += NT)
+        if (S != 0.0) ts += qm[DS + j] - sm[1 + DS + j] * (sm[1 + DS + j] / S);
     // fixed-order block sums (wave shuffles, then one value per wave)
     for (int o = 32; o > 0; o >>= 1) {
         t1 += __shfl_xor(t1, o);
         t2 += __shfl_xor(t2, o);
+        ts += __shfl_xor(ts, o);
     }
-    if ((tid & 63) == 0) {
-        red[0][tid >> 6] = t1;
-        red[1][tid >> 6] = t2;
+    if (lane == 0) {
+        red[0][wave] = t1;
+        red[1][wave] = t2;
+        red[2][wave] = ts;
     }
     __syncthreads();
     if (tid == 0) {
-        double tr1 = 0.0, tr2 = 0.0;
-        for (int w = 0; w < 256 / 64; ++w) {
+        double tr1 = 0.0, tr2 = 0.0, tss = 0.0;
+        for (int w = 0; w < RB; ++w) {
             tr1 += red[0][w];
             tr2 += red[1][w];
+            tss += red[2][w];
         }
-        const double S = sm[0];
-        double tss = 0.0;
-        if (S != 0.0)
-            for (int j = 0; j < d_t; ++j) tss += qm[d_s + j] - sm[1 + d_s + j] * (sm[1 + d_s + j] / S);
         r2[m] = tss > 0.0 ? 1.0 - (tss - 2.0 * tr1 + tr2) / tss : 0.0;
     }
+}
+
+template <int DS, int DT>
+hipError_t launch_probe_r2_t(int32_t n_maps, const double *sums, const double *sq, const float *A, const float *B,
+                             const float *maps, double *r2, hipStream_t s) {
+    hipLaunchKernelGGL((probe_r2_kernel<DS, DT>), dim3(n_maps), dim3(2 * DS), 0, s, sums, sq, A, B, maps, r2);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -99,9 +123,7 @@ __global__ __launch_bounds__(256) void probe_r2_kernel(int d_s, int d_t, const d
 hipError_t launch_probe_r2(int32_t n_maps, int32_t d_s, int32_t d_t, const double *sums, const double *sq,
                            const float *A, const float *B, const float *maps, double *r2, hipStream_t s) {
     if (n_maps == 0) return hipSuccess;
-    if (d_s > kMaxD || d_t > kMaxD || d_t % 8 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(probe_r2_kernel, dim3(n_maps), dim3(256), 0, s, d_s, d_t, sums, sq, A, B, maps, r2);
-    return hipGetLastError();
+    CB_DISPATCH(launch_probe_r2_t, d_s, d_t, n_maps, sums, sq, A, B, maps, r2, s);
 }
 
 }  // namespace cb

@@ -862,17 +862,3 @@ void stats_kernel(StatsArgs a) {
 }  // namespace
 }  // namespace cb
 
-// Host dispatch of a launcher template over the supported (d_s, d_t) pairs.
-#define CB_DISPATCH(FN, d_s, d_t, ...)                                        \
-    switch ((d_s) * 1000 + (d_t)) {                                          \
-        case 64064: return FN<64, 64>(__VA_ARGS__);                          \
-        case 64096: return FN<64, 96>(__VA_ARGS__);                          \
-        case 64128: return FN<64, 128>(__VA_ARGS__);                         \
-        case 96064: return FN<96, 64>(__VA_ARGS__);                          \
-        case 96096: return FN<96, 96>(__VA_ARGS__);                          \
-        case 96128: return FN<96, 128>(__VA_ARGS__);                         \
-        case 128064: return FN<128, 64>(__VA_ARGS__);                        \
-        case 128096: return FN<128, 96>(__VA_ARGS__);                        \
-        case 128128: return FN<128, 128>(__VA_ARGS__);                       \
-        default: return hipErrorInvalidValue;                                \
-    }

@@ -123,3 +123,28 @@ def test_wide_solve_centered_shapes(cb, dx):
     assert (info.cpu().numpy() == 0).all() and (io == 0).all()
     for m in range(n):
         assert _relF(maps[m].double().cpu().numpy(), W[m]) < 1e-6
+
+
+# Probe R^2 for every width pair against the same formula in fp64.  The kernel forms A W with fp32 sums of d_s
+# products: each element is off by at most d_s 2^-24 sum |A_ik W_kj|, hence the bound on tr(W^T A W) below.
+@pytest.mark.parametrize("dt", [64, 96, 128])
+@pytest.mark.parametrize("ds", [64, 96, 128])
+def test_probe_r2_widths(cb, ds, dt):
+    n = 5
+    rng = np.random.default_rng(ds * dt)
+    A, B = _moments(n, ds, dt, ds + dt)
+    W = (rng.standard_normal((n, ds + 1, dt)) / ds).astype(np.float32)
+    sums = np.concatenate([np.full((n, 1), 3.0 * ds), rng.standard_normal((n, ds + dt))], axis=1)
+    sq = np.abs(rng.standard_normal((n, ds + dt))) * 1e4
+    sums[4] = 0.0                                          # no data: R^2 is 0
+    sq[3] = 0.0                                            # no variance: R^2 is 0
+    r2 = torch.full((n,), 9.0, dtype=torch.float64, device="cuda")
+    cb.cb_probe_r2(*(torch.from_numpy(x).cuda() for x in (sums, sq, A, B, W)), r2)
+    got = r2.cpu().numpy()
+    for m in range(3):
+        w, a = W[m, :ds].astype(np.float64), A[m].astype(np.float64)
+        tss = (sq[m, ds:] - sums[m, 1 + ds:] ** 2 / sums[m, 0]).sum()
+        rss = tss - 2 * (w * B[m]).sum() + (w * (a @ w)).sum()
+        bound = ds * 2.0 ** -24 * (np.abs(w) * (np.abs(a) @ np.abs(w))).sum() / tss
+        assert abs(got[m] - (1 - rss / tss)) <= bound + 1e-12
+    assert got[3] == 0.0 and got[4] == 0.0
