@@ -109,6 +109,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
             ii[q] = 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
             jj[q] = l & 31;
             float acc = 0.f;
+#pragma unroll 8
             for (int ch = 0; ch < a.n_chunks; ++ch) acc += base[ch * chunk_stride + job * 1024 + f];
             sum[q] = acc;
         }

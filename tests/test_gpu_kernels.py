@@ -148,3 +148,42 @@ def test_probe_r2_widths(cb, ds, dt):
         bound = ds * 2.0 ** -24 * (np.abs(w) * (np.abs(a) @ np.abs(w))).sum() / tss
         assert abs(got[m] - (1 - rss / tss)) <= bound + 1e-12
     assert got[3] == 0.0 and got[4] == 0.0
+
+
+# Token tiles of a call cut into chunks by size: one chunk per item, several, a last chunk shorter than the others, and
+# tiles that end inside a sequence; 3 target layers of 2 heads leave a chip-filling number of chunks, 300 maps do not.
+# fp32 sums of exact products with the weight in two bf16 terms: 1e-5 is ten times what the largest call shows.
+@pytest.mark.parametrize("layers,seqs,T", [(3, 1, 31), (3, 1, 2048), (3, 5, 333), (75, 1, 1000), (75, 3, 700)])
+@pytest.mark.parametrize("centered", [False, True])
+def test_stats_chunks(cb, layers, seqs, T, centered):
+    H, d = 2, 64
+    rows = [(l, h, z, l % 5, h, l * H + h) for l in range(layers) for z in range(2) for h in range(H)]
+    names = ("tgt_layer", "tgt_head", "kv", "src_layer", "src_head", "weight_row")
+    hm = {k: np.asarray(v, dtype=np.int32) for k, v in zip(names, zip(*rows))}
+    n, g = len(rows), torch.Generator(device="cuda").manual_seed(seqs * T)
+    src = torch.randn((5, 2, seqs, H, T, d), generator=g, device="cuda").bfloat16()
+    tgt = torch.randn((layers, 2, seqs, H, T, d), generator=g, device="cuda").bfloat16()
+    w = torch.rand((layers * H, seqs * T), generator=g, device="cuda")
+    plan = cb.cb_plan_create(hm, src, tgt, seqs * T)
+    ref = []
+    for l, h, z, sl, sh, wr in rows:
+        x = src[sl, z, :, sh].reshape(-1, d).double()
+        y = tgt[l, z, :, h].reshape(-1, d).double()
+        ww = w[wr].double()[:, None]
+        if centered:
+            x, y = x - (ww * x).sum(0) / ww.sum(), y - (ww * y).sum(0) / ww.sum()
+        else:
+            x = torch.cat([x, torch.ones_like(x[:, :1])], dim=1)
+        ref.append(((x * ww).t() @ x, (x * ww).t() @ y))
+    P = d if centered else d + 1
+    G, C = torch.ones((n, P, P), device="cuda"), torch.ones((n, P, d), device="cuda")
+    if centered:
+        sums = torch.zeros((n, 1 + 2 * d), dtype=torch.float64, device="cuda")
+        cb.cb_stats_means(plan, src, tgt, w, sums)
+        cb.cb_stats_accumulate_centered(plan, src, tgt, w, sums, G, C)
+    else:
+        cb.cb_stats_accumulate(plan, src, tgt, w, G, C)
+    assert torch.equal(G, G.transpose(1, 2))
+    for m, (rg, rc) in enumerate(ref):
+        for got, want in ((G[m], rg + 1), (C[m], rc + 1)):           # added to what was there
+            assert float((got.double() - want).norm() / want.norm()) < 1e-5, (m, layers, seqs, T)
