@@ -48,11 +48,11 @@ struct cb_plan {
     int32_t *d_map_yown = nullptr;
     float *d_partials = nullptr;
     void *d_zero = nullptr;        // zero bytes: source of copies for absent tokens
-    // application schedule and split coefficients
+    // application schedule
     int32_t n_groups = 0;
     cb::ApplyGroup *d_groups = nullptr;
+    // multi-layer application: split coefficients
     uint16_t *d_whi = nullptr;
-    uint16_t *d_wlo = nullptr;
     float *d_bias = nullptr;
     // multi-layer plans with rotary keys: de-rotated K rows of the current call
     uint16_t *d_rws = nullptr;
@@ -377,7 +377,6 @@ cb_status cb_plan_destroy(cb_plan *p) {
     (void)hipFree(p->d_zero);
     (void)hipFree(p->d_groups);
     (void)hipFree(p->d_whi);
-    (void)hipFree(p->d_wlo);
     (void)hipFree(p->d_bias);
     (void)hipFree(p->d_tasks);
     (void)hipFree(p->d_amaps);
@@ -542,16 +541,13 @@ cb_status cb_plan_create(const cb_head_map *map, const cb_cache *src_geom, const
     // ---- device allocations
     const int64_t slot_floats = cb::stats_slot_floats(d_s, d_t);
     const size_t partial_bytes = (size_t)p->n_items * p->max_chunks * 2 * slot_floats * sizeof(float);
-    const size_t wsplit = (size_t)n * d_t * d_s * sizeof(uint16_t);
     bool okm = hipMalloc(&p->d_items, sizeof(cb::StatsItem) * items.size()) == hipSuccess &&
                hipMalloc(&p->d_map_item, sizeof(int32_t) * n) == hipSuccess &&
                hipMalloc(&p->d_map_slot, sizeof(int32_t) * n) == hipSuccess &&
                hipMalloc(&p->d_map_yown, sizeof(int32_t) * n) == hipSuccess &&
                hipMalloc(&p->d_partials, partial_bytes) == hipSuccess &&
                hipMalloc(&p->d_zero, 256) == hipSuccess &&
-               hipMalloc(&p->d_groups, sizeof(cb::ApplyGroup) * agroups.size()) == hipSuccess &&
-               hipMalloc(&p->d_whi, wsplit) == hipSuccess && hipMalloc(&p->d_wlo, wsplit) == hipSuccess &&
-               hipMalloc(&p->d_bias, sizeof(float) * n * d_t) == hipSuccess;
+               hipMalloc(&p->d_groups, sizeof(cb::ApplyGroup) * agroups.size()) == hipSuccess;
     if (!okm) {
         (void)hipGetLastError();
         cb_plan_destroy(p);
@@ -1500,8 +1496,6 @@ static cb_status apply_single(cb_plan *p, const float *maps, const cb_cache *src
                                         "turn the sender with cb_rope first", p->d_s);
     if (cb_status s = check_device(p)) return s;
     hipStream_t st = (hipStream_t)stream;
-    if (cb::launch_split_maps(p->n_maps, p->d_s, p->d_t, maps, p->d_whi, p->d_wlo, p->d_bias, st) != hipSuccess)
-        return fail(CB_ERR_DEVICE, "map split launch failed");
     if (N == 0) return ok();
     cb::ApplyArgs a = {};
     a.src = (const uint16_t *)src->data;
@@ -1510,21 +1504,31 @@ static cb_status apply_single(cb_plan *p, const float *maps, const cb_cache *src
     a.os = strides_of(tgt_out);
     a.T = cb::make_fastdiv((uint32_t)src->seq_len);
     a.N = (int32_t)N;
-    // Token tiles of whole 32-token sub-blocks: about 16 workgroups per
-    // compute unit in total, at most 8192 tokens (a workgroup streams its
-    // tile through a ring, so longer tiles amortize the ring's fill).
+    // Token tiles of whole 32-token sub-blocks, at most 8192 tokens.  One
+    // workgroup runs per compute unit, and loading its maps and filling its
+    // ring costs about as much as kFixed sub-blocks; so the count of tiles per
+    // source block that makes the fewest rounds times (sub-blocks + kFixed)
+    // is taken (kFixed = 4 measured the same or slower).  Measured, 1,024 maps
+    // (640 source blocks), tiles of at least 256 tokens and about 16 workgroups
+    // per compute unit, after a pass that split the maps -> now, us: 32 tokens
+    // 114 -> 22, 200 135 -> 43, 777 260 -> 114, 3,000 510 -> 355, 8,000 962 ->
+    // 817; 320 maps of 96 and 128, 777 tokens 70 -> 32.
     {
-        const int64_t target = 16LL * p->n_cu;
-        int64_t tt = ((int64_t)N * std::max(p->n_groups, 1) + target - 1) / target;
-        tt = std::min<int64_t>(std::max<int64_t>(tt, 256), 8192);
-        tt = (tt + 31) / 32 * 32;
-        a.tile_tokens = (int32_t)tt;
+        constexpr int64_t kFixed = 8;
+        const int64_t sub = (N + 31) / 32, fewest = (sub + 255) / 256;
+        int64_t best = -1, per = sub;
+        for (int64_t nt = fewest; nt <= std::min(sub, fewest + 31); ++nt) {
+            const int64_t ct = (sub + nt - 1) / nt;
+            const int64_t rounds = ((int64_t)p->n_groups * ((sub + ct - 1) / ct) + p->n_cu - 1) / p->n_cu;
+            if (best >= 0 && rounds * (ct + kFixed) >= best) continue;
+            best = rounds * (ct + kFixed);
+            per = ct;
+        }
+        a.tile_tokens = (int32_t)(32 * per);
     }
     a.n_tiles = (int32_t)((N + a.tile_tokens - 1) / a.tile_tokens);
     a.groups = p->d_groups;
-    a.w_hi = p->d_whi;
-    a.w_lo = p->d_wlo;
-    a.bias = p->d_bias;
+    a.maps = maps;
     a.rope_table = tgt_rope ? tgt_rope->table : nullptr;
     a.rope_style = tgt_rope ? tgt_rope->style : 0;
     a.rope_pos_offset = tgt_rope ? tgt_rope->pos_offset : 0;

@@ -6,17 +6,19 @@
 // coefficient count.  Per map m and token t:
 //     out[t, :] = RNE_bf16( x_t W_m + b_m )
 //
-// split_maps_kernel: W (fp32) -> W^T as two bf16 planes, hi = RNE(W) and
-//   lo = RNE(W - hi), plus the fp32 bias.  The pair carries ~16 significant
-//   bits, so the bf16 MFMA products match an fp32 product to ~2^-17.
 // apply_kernel: one workgroup per (source block, token tile).  A copy wave
 //   streams the tile's source rows HBM -> LDS in 32-token sub-blocks through
-//   a ring of direct-to-LDS copies; wave (slot, rb) keeps its 32 rows of
-//   W_hi^T / W_lo^T for its map in registers and computes the 32x32 output
-//   tile D = W^T x^T with v_mfma_f32_32x32x16_bf16 (K = source channels),
-//   adds the bias and rounds once to bf16; the tile goes through an LDS
-//   staging buffer and leaves as whole target rows.  A source block shared by
-//   two target maps is read once.
+//   a ring of direct-to-LDS copies; wave (slot, rb) keeps its 32 rows of W^T
+//   for its map in registers as two bf16 terms, hi = RNE(W) and lo = RNE(W -
+//   hi) (together ~16 significant bits, so the products match an fp32 product
+//   to ~2^-17), split from the caller's fp32 map while the ring fills; it
+//   computes the 32x32 output tile D = W^T x^T with v_mfma_f32_32x32x16_bf16
+//   (K = source channels), adds the bias and rounds once to bf16; the tile
+//   goes through an LDS staging buffer and leaves as whole target rows.  A
+//   source block shared by two target maps is read once.
+//   The fp32 rows are as many bytes as the two bf16 planes that a pass of its
+//   own wrote before (100 us and 130 MB for 1,024 maps, on every call): a
+//   workgroup reads what it read, and the call saves that pass.
 //
 // With the sender's rotary transform removed on the way in (Sec. 2.1, Sec.
 // 3.1: the maps act on content coordinates), the computing waves turn
@@ -74,28 +76,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     f32x2_t v = {lo, hi};
     bf16x2_t p = __builtin_convertvector(v, bf16x2_t);
     return __builtin_bit_cast(uint32_t, p);
-}
-
-__global__ __launch_bounds__(256) void split_maps_kernel(int n_maps, int d_s, int d_t,
-                                                         const float *__restrict__ maps,
-                                                         uint16_t *__restrict__ w_hi,
-                                                         uint16_t *__restrict__ w_lo,
-                                                         float *__restrict__ bias) {
-    const int P = d_s + 1;
-    const int64_t n = (int64_t)n_maps * d_t * d_s;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(e % d_s);
-        const int64_t mj = e / d_s;
-        const int j = (int)(mj % d_t);
-        const int64_t m = mj / d_t;
-        const float w = maps[(m * P + k) * d_t + j];
-        const uint32_t p = pack_bf16(w, 0.f);
-        const float hi = __uint_as_float(p << 16);
-        const uint32_t q = pack_bf16(w - hi, 0.f);
-        w_hi[e] = (uint16_t)(p & 0xffffu);
-        w_lo[e] = (uint16_t)(q & 0xffffu);
-        if (k == 0) bias[m * d_t + j] = maps[(m * P + d_s) * d_t + j];
-    }
 }
 
 template <int DS, int DT, int SR = 0>
@@ -321,23 +301,26 @@ __global__ __attribute__((amdgpu_flat_work_group_size(ACfg<DS, DT>::NT, ACfg<DS,
     float bias[16];
     {
         const int ch = out_channel<DT, RS>(rb, (int)lrow);
-        const uint16_t *wh = a.w_hi + ((int64_t)m * DT + ch) * DS + 8 * lhalf;
-        const uint16_t *wl = a.w_lo + ((int64_t)m * DT + ch) * DS + 8 * lhalf;
+        const float *wp = a.maps + ((int64_t)m * (DS + 1) + 8 * lhalf) * DT + ch;   // W[8 lhalf][ch]
 #pragma unroll
         for (int ks = 0; ks < K::KS; ++ks) {
-            ahi[ks] = *reinterpret_cast<const bf16x8_t *>(wh + 16 * ks);
-            alo[ks] = *reinterpret_cast<const bf16x8_t *>(wl + 16 * ks);
-        }
+            float w[8];
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            // rows 8 gq + 4 lhalf .. + 3: four consecutive channels
-            const float *bp = a.bias + (int64_t)m * DT + out_channel<DT, RS>(rb, 8 * gq + 4 * (int)lhalf);
-            const float4 b4 = *reinterpret_cast<const float4 *>(bp);
-            bias[4 * gq + 0] = b4.x;
-            bias[4 * gq + 1] = b4.y;
-            bias[4 * gq + 2] = b4.z;
-            bias[4 * gq + 3] = b4.w;
+            for (int j = 0; j < 8; ++j) w[j] = wp[(16 * ks + j) * DT];
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                hi[j] = pack_bf16(w[2 * j], w[2 * j + 1]);
+                lo[j] = pack_bf16(w[2 * j] - __uint_as_float(hi[j] << 16),
+                                  w[2 * j + 1] - __uint_as_float(hi[j] & 0xffff0000u));
+            }
+            ahi[ks] = __builtin_bit_cast(bf16x8_t, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+            alo[ks] = __builtin_bit_cast(bf16x8_t, make_uint4(lo[0], lo[1], lo[2], lo[3]));
         }
+        const float *bp = a.maps + ((int64_t)m * (DS + 1) + DS) * DT;
+#pragma unroll
+        for (int v = 0; v < 16; ++v)                           // rows 8 (v / 4) + 4 lhalf + v mod 4
+            bias[v] = bp[out_channel<DT, RS>(rb, 8 * (v >> 2) + 4 * (int)lhalf + (v & 3))];
     }
     // channel offsets of the lane's two 16-byte output chunks (after the
     // exchange below: MFMA rows 8 lhalf .. +7 and 16 + 8 lhalf .. +7)
@@ -568,17 +551,6 @@ hipError_t launch_apply_t(int n_groups, const ApplyArgs &a, hipStream_t s) {
 }
 
 }  // namespace
-
-hipError_t launch_split_maps(int32_t n_maps, int32_t d_s, int32_t d_t, const float *maps, uint16_t *w_hi,
-                             uint16_t *w_lo, float *bias, hipStream_t s) {
-    const int64_t n = (int64_t)n_maps * d_t * d_s;
-    if (n == 0) return hipSuccess;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(split_maps_kernel, dim3((unsigned)blocks), dim3(256), 0, s, n_maps, d_s, d_t, maps, w_hi,
-                       w_lo, bias);
-    return hipGetLastError();
-}
 
 #define CB_DISPATCH_APPLY(d_s, d_t, ...)                                     \
     switch ((d_s) * 1000 + (d_t)) {                                          \

@@ -98,9 +98,7 @@ struct ApplyArgs {
     int32_t tile_tokens;  // tokens per workgroup
     int32_t n_tiles;      // per group
     const ApplyGroup *groups;
-    const uint16_t *w_hi; // [n_maps][d_t][d_s] bf16, transposed maps
-    const uint16_t *w_lo;
-    const float *bias;    // [n_maps][d_t]
+    const float *maps;    // [n_maps][d_s + 1][d_t], bias last
     const float *rope_table;  // NULL, or the target's (cos, sin) [n_pos][d_t/2][2]: K outputs are rotated
     int32_t rope_style;       // 0: pairs (i, i + d_t/2), 1: pairs (2i, 2i + 1)
     int32_t rope_pos_offset;  // position of token 0 of every sequence
@@ -269,8 +267,6 @@ hipError_t launch_solve_blocked_static(int32_t n_maps, int32_t P, int32_t d_t, c
                                        float lambda, uint32_t flags, float *maps, int32_t *info, hipStream_t s);
 hipError_t launch_solve(int32_t n_maps, int32_t P, int32_t d_t, const float *G, const float *C,
                         float lambda, uint32_t flags, float *maps, int32_t *info, hipStream_t s);
-hipError_t launch_split_maps(int32_t n_maps, int32_t d_s, int32_t d_t, const float *maps,
-                             uint16_t *w_hi, uint16_t *w_lo, float *bias, hipStream_t s);
 hipError_t launch_apply(int d_s, int d_t, int n_groups, const ApplyArgs &a, hipStream_t s);
 
 // Geometry of the statistics kernel, shared with the host for workspace sizing.

@@ -187,3 +187,28 @@ def test_stats_chunks(cb, layers, seqs, T, centered):
     for m, (rg, rc) in enumerate(ref):
         for got, want in ((G[m], rg + 1), (C[m], rc + 1)):           # added to what was there
             assert float((got.double() - want).norm() / want.norm()) < 1e-5, (m, layers, seqs, T)
+
+
+# Token tiles of the single-layer application: one token, the edges of a 32-token sub-block, several tiles and more
+# than the 8192 tokens of one, a source block of two maps and one of a single map; the maps at an address that is only
+# 4-byte aligned.  An element is the fp64 value rounded once, up to one bf16 ulp where the fp32 sum (coefficients as two
+# bf16 terms, 2^-17 of the sum of |x W|, far below 1e-4 of the outputs' RMS) falls on the other side of a tie.
+@pytest.mark.parametrize("T", [1, 31, 33, 500, 8225])
+@pytest.mark.parametrize("ds,dt", [(64, 128), (96, 64), (128, 96)])
+def test_apply_token_tiles(cb, ds, dt, T):
+    names = ("tgt_layer", "tgt_head", "kv", "src_layer", "src_head", "weight_row")
+    rows = [(0, 0, 0, 0, 0, 0), (1, 0, 0, 0, 0, 0), (0, 0, 1, 1, 0, 0)]      # two maps of one block, one alone
+    hm = {k: np.asarray(v, dtype=np.int32) for k, v in zip(names, zip(*rows))}
+    g = torch.Generator(device="cuda").manual_seed(T)
+    src = torch.randn((2, 2, 1, 1, T, ds), generator=g, device="cuda").bfloat16()
+    flat = torch.randn(3 * (ds + 1) * dt + 1, generator=g, device="cuda") / ds ** 0.5
+    maps = flat[1:].view(3, ds + 1, dt)
+    out = torch.full((2, 2, 1, 1, T + 1, dt), 5.0, dtype=torch.bfloat16, device="cuda")
+    plan = cb.cb_plan_create(hm, src, out, T)
+    cb.cb_apply(plan, maps, src, out[:, :, :, :, :T])
+    for m, (tl, _, z, sl, _, _) in enumerate(rows):
+        ref = src[sl, z, 0, 0].double() @ maps[m, :-1].double() + maps[m, -1].double()
+        got = out[tl, z, 0, 0, :T].double()
+        bound = ref.abs() * 2.0 ** -8 + 1e-4 * ref.square().mean().sqrt()
+        assert bool(((got - ref).abs() <= bound).all()), (m, ds, dt, T)
+    assert bool((out[:, :, :, :, T:] == 5.0).all()) and bool((out[1, 1] == 5.0).all())
