@@ -212,3 +212,38 @@ def test_apply_token_tiles(cb, ds, dt, T):
         bound = ref.abs() * 2.0 ** -8 + 1e-4 * ref.square().mean().sqrt()
         assert bool(((got - ref).abs() <= bound).all()), (m, ds, dt, T)
     assert bool((out[:, :, :, :, T:] == 5.0).all()) and bool((out[1, 1] == 5.0).all())
+
+
+# Multi-layer moments of a call long enough to be added into G and C twice (every 32,736 rows) and of the shortest
+# ones, k with a half-used task rectangle among them; what was in G and C stays.  1e-5: fp32 sums over 32,736 rows.
+@pytest.mark.parametrize("k,T,stride", [(2, 33001, 1), (3, 17, 4), (1, 5, 1), (5, 131, 2)])
+@pytest.mark.parametrize("centered", [False, True])
+def test_multi_stats_flushes(cb, k, T, stride, centered):
+    d, L, n = 128, 6, 2
+    hm = dict(tgt_layer=[0, 0], tgt_head=[0, 0], kv=[0, 1], src_layers=[[(2 * j + m) % L for j in range(k)] for m in range(n)],
+              src_head=[0, 0], weight_row=[0, 1])
+    if k == 5:
+        hm["src_layers"] = [[0, 1, 2, 3, 4], [5, 4, 3, 2, 1]]
+    g = torch.Generator(device="cuda").manual_seed(T)
+    src = torch.randn((L, 2, 1, 1, T, d), generator=g, device="cuda").bfloat16()
+    tgt = torch.randn((1, 2, 1, 1, T, d), generator=g, device="cuda").bfloat16()
+    w = torch.rand((2, T), generator=g, device="cuda")
+    plan = cb.cb_plan_create_multi(hm, src, tgt, stride)
+    P = k * d + (0 if centered else 1)
+    G, C = torch.ones((n, P, P), device="cuda"), torch.ones((n, P, d), device="cuda")
+    if centered:
+        sums = torch.zeros((n, 1 + P + d), dtype=torch.float64, device="cuda")
+        cb.cb_stats_means(plan, src, tgt, w, sums)
+        cb.cb_stats_accumulate_centered(plan, src, tgt, w, sums, G, C)
+    else:
+        cb.cb_stats_accumulate(plan, src, tgt, w, G, C)
+    assert torch.equal(G, G.transpose(1, 2))
+    for m in range(n):
+        x = torch.cat([src[j, m, 0, 0, ::stride].double() for j in hm["src_layers"][m]], dim=1)
+        y, ww = tgt[0, m, 0, 0, ::stride].double(), w[m, ::stride].double()[:, None]
+        if centered:
+            x, y = x - (ww * x).sum(0) / ww.sum(), y - (ww * y).sum(0) / ww.sum()
+        else:
+            x = torch.cat([x, torch.ones_like(x[:, :1])], dim=1)
+        for got, want in ((G[m], (x * ww).t() @ x + 1), (C[m], (x * ww).t() @ y + 1)):
+            assert float((got.double() - want).norm() / want.norm()) < 1e-5
