@@ -165,6 +165,19 @@ cb_status check_cache(const char *name, const cb_cache *c, int L, int H, int d) 
     return CB_OK;
 }
 
+// Consecutive units on one XCD where maps share target rows (layer-selection
+// probes: every target block is read with each candidate source layer, every
+// source block with each target layer).  The items are then ordered by (K/V,
+// source head, source layer), so the units an XCD runs together read few blocks
+// many times, out of its L2.  Plans that read every target block once keep the
+// round-robin order: their units have nothing to share beyond an item.  Measured,
+// 10,240 probes (16 target x 40 source layers), 4,096 tokens: second pass 5.0 ->
+// 4.7 ms, means 2.31 -> 2.18 ms (5.2 and 2.90 ms with the consecutive units alone,
+// the items in the caller's order).
+int32_t units_per_xcd(const cb_plan *p, int n_chunks) {
+    return p->duplicate_targets ? (int32_t)(((int64_t)p->n_items * n_chunks + 7) / 8) : 0;
+}
+
 cb::Strides strides_of(const cb_cache *c) { return {c->s_layer, c->s_kv, c->s_seq, c->s_head, c->s_tok}; }
 
 // Validation and work units shared by the statistics calls.  *empty is set
@@ -205,6 +218,7 @@ cb_status prepare_stats(const cb_plan *p, const cb_cache *src, const cb_cache *t
                         &a.chunk_tiles);
     if (a.n_chunks > p->max_chunks) return fail(CB_ERR_UNSUPPORTED, "internal: chunk count exceeds workspace");
     a.n_items = p->n_items;
+    a.per_xcd = units_per_xcd(p, a.n_chunks);
     a.items = p->d_items;
     a.partials = p->d_partials;
     a.zero = p->d_zero;
@@ -450,6 +464,12 @@ cb_status cb_plan_create(const cb_head_map *map, const cb_cache *src_geom, const
             groups[it->second].push_back(m);
         }
     }
+
+    if (duplicate)                                            // (see units_per_xcd)
+        std::stable_sort(groups.begin(), groups.end(), [&](const std::vector<int> &a, const std::vector<int> &b) {
+            return std::make_tuple(map->kv[a[0]], map->src_head[a[0]], map->src_layer[a[0]]) <
+                   std::make_tuple(map->kv[b[0]], map->src_head[b[0]], map->src_layer[b[0]]);
+        });
 
     // Target sums (sum w y, sum w y^2) depend only on the target block and the
     // weight row: the first map of each such pair carries them for all of its
@@ -1077,6 +1097,7 @@ cb_status cb_stats_means(cb_plan *p, const cb_cache *src, const cb_cache *tgt, c
         const int64_t cap = (int64_t)p->max_chunks * cb::stats_slot_floats(p->d_s, p->d_t) / (2 * ne);
         choose_chunks(a.n_tiles, p->n_items, p->n_cu, (int)std::min<int64_t>(cap, 1 << 20), &a.n_chunks,
                       &a.chunk_tiles, 16);
+        a.per_xcd = units_per_xcd(p, a.n_chunks);
     }
     if (cb::launch_means(p->d_s, p->d_t, a, sq != nullptr, st) != hipSuccess)
         return fail(CB_ERR_DEVICE, "means kernel launch failed");

@@ -64,6 +64,7 @@ struct StatsArgs {
     int32_t chunk_tiles;  // tiles per work unit
     int32_t n_chunks;
     int32_t n_items;
+    int32_t per_xcd;      // 0: block b runs unit b; else the blocks of XCD x run units x per_xcd .. (see stats_unit)
     const StatsItem *items;
     float *partials;      // [n_chunks * n_items][2][slot_floats]
     const void *zero;     // >= 256 zero bytes: source of the weights of absent tokens
@@ -76,6 +77,13 @@ struct StatsArgs {
     int32_t rope_pos[2];
     int32_t rope_on[2];
 };
+
+// Workgroups go round-robin over the eight XCDs; with per_xcd set each XCD runs
+// consecutive units (chunk-major, item-minor).
+__device__ __forceinline__ int stats_unit(const StatsArgs &a, int b) {
+    return a.per_xcd ? (b & 7) * a.per_xcd + (b >> 3) : b;
+}
+inline int stats_grid(const StatsArgs &a) { return a.per_xcd ? 8 * a.per_xcd : a.n_items * a.n_chunks; }
 
 struct ReduceArgs {
     const float *partials;

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float *p, int64_t n) {
 template <int DS, int DT>
 hipError_t launch_stats_t(const StatsArgs &a, hipStream_t s) {
     using K = Cfg<DS, DT>;
-    const int grid = a.n_items * a.n_chunks;
+    const int grid = stats_grid(a);
     if (grid == 0) return hipSuccess;
     if (a.seq_len % K::KT == 0)
         hipLaunchKernelGGL((stats_kernel<DS, DT, false, false>), dim3(grid), dim3(K::NT), 0, s, a);

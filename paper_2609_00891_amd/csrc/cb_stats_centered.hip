@@ -139,7 +139,8 @@ void means_kernel(StatsArgs a) {
     using M = MCfg<DS, DT, SQ>;
     constexpr int NE = M::NE;
     __shared__ double red[M::MAXR][2 * NE];
-    const int unit = blockIdx.x;
+    const int unit = stats_unit(a, blockIdx.x);
+    if (unit >= a.n_items * a.n_chunks) return;
     const int item_id = unit % a.n_items, chunk = unit / a.n_items;
     const StatsItem *it = a.items + item_id;
     const int n_slots = it->n_slots;
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(256) void means_reduce_kernel(ReduceArgs a) {
 
 template <int DS, int DT>
 hipError_t launch_means_t(const StatsArgs &a, bool sq, hipStream_t s) {
-    const int grid = a.n_items * a.n_chunks;
+    const int grid = stats_grid(a);
     if (grid == 0) return hipSuccess;
     if (sq) hipLaunchKernelGGL((means_kernel<DS, DT, true>), dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((means_kernel<DS, DT, false>), dim3(grid), dim3(256), 0, s, a);
@@ -205,7 +206,7 @@ hipError_t launch_means_reduce_t(const ReduceArgs &a, hipStream_t s) {
 template <int DS, int DT>
 hipError_t launch_stats_centered_t(const StatsArgs &a, hipStream_t s) {
     using K = Cfg<DS, DT>;
-    const int grid = a.n_items * a.n_chunks;
+    const int grid = stats_grid(a);
     if (grid == 0) return hipSuccess;
     if (a.seq_len % K::KT == 0)
         hipLaunchKernelGGL((stats_kernel<DS, DT, false, true>), dim3(grid), dim3(K::NT), 0, s, a);

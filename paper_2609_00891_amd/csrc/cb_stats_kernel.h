@@ -834,7 +834,8 @@ void stats_kernel(StatsArgs a) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     StatsCtx c;
-    c.unit = blockIdx.x;
+    c.unit = stats_unit(a, blockIdx.x);
+    if (c.unit >= a.n_items * a.n_chunks) return;
     const int item_id = c.unit % a.n_items;
     const int chunk = c.unit / a.n_items;
     const StatsItem it = a.items[item_id];

@@ -13,7 +13,7 @@ namespace {
 template <int D, int RS>
 hipError_t launch_stats_rope_t(const StatsArgs &a, hipStream_t s) {
     using K = Cfg<D, D>;
-    const int grid = a.n_items * a.n_chunks;
+    const int grid = stats_grid(a);
     if (grid == 0) return hipSuccess;
     if (a.seq_len % K::KT == 0)
         hipLaunchKernelGGL((stats_kernel<D, D, false, false, RS>), dim3(grid), dim3(K::NT), 0, s, a);

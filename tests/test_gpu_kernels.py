@@ -247,3 +247,34 @@ def test_multi_stats_flushes(cb, k, T, stride, centered):
             x = torch.cat([x, torch.ones_like(x[:, :1])], dim=1)
         for got, want in ((G[m], (x * ww).t() @ x + 1), (C[m], (x * ww).t() @ y + 1)):
             assert float((got.double() - want).norm() / want.norm()) < 1e-5
+
+
+# Plans whose maps share target rows (every target layer with every source layer), their units in consecutive runs per
+# XCD: fewer units than XCDs, counts that are no multiple of eight, one chunk and several.  1e-5 as for the chunks.
+@pytest.mark.parametrize("Lt,Ls,H,T", [(2, 1, 1, 33), (1, 3, 1, 500), (3, 5, 1, 2100), (5, 7, 2, 130)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_stats_shared_targets(cb, d, Lt, Ls, H, T):
+    rows = [(l, h, z, s, h, l * H + h) for l in range(Lt) for s in range(Ls) for z in range(2) for h in range(H)]
+    rows += rows[:1]                                                    # one map twice: shared targets at Ls = 1 too
+    names = ("tgt_layer", "tgt_head", "kv", "src_layer", "src_head", "weight_row")
+    hm = {k: np.asarray(v, dtype=np.int32) for k, v in zip(names, zip(*rows))}
+    n, g = len(rows), torch.Generator(device="cuda").manual_seed(T)
+    src = torch.randn((Ls, 2, 2, H, T, d), generator=g, device="cuda").bfloat16()
+    tgt = torch.randn((Lt, 2, 2, H, T, d), generator=g, device="cuda").bfloat16()
+    w = torch.rand((Lt * H, 2 * T), generator=g, device="cuda")
+    plan = cb.cb_plan_create(hm, src, tgt, 2 * T)
+    G, C = torch.zeros((n, d + 1, d + 1), device="cuda"), torch.zeros((n, d + 1, d), device="cuda")
+    A, B = torch.zeros((n, d, d), device="cuda"), torch.zeros((n, d, d), device="cuda")
+    sums = torch.zeros((n, 1 + 2 * d), dtype=torch.float64, device="cuda")
+    sq = torch.zeros((n, 2 * d), dtype=torch.float64, device="cuda")
+    cb.cb_stats_accumulate(plan, src, tgt, w, G, C)
+    cb.cb_stats_means(plan, src, tgt, w, sums, sq=sq)
+    cb.cb_stats_accumulate_centered(plan, src, tgt, w, sums, A, B)
+    for m, (l, h, z, s, _, wr) in enumerate(rows):
+        x, y, ww = src[s, z, :, h].reshape(-1, d).double(), tgt[l, z, :, h].reshape(-1, d).double(), w[wr].double()[:, None]
+        x1, xy = torch.cat([x, torch.ones_like(x[:, :1])], dim=1), torch.cat([x, y], dim=1)
+        xc, yc = x - (ww * x).sum(0) / ww.sum(), y - (ww * y).sum(0) / ww.sum()
+        s1 = torch.cat([ww.sum(0), (ww * xy).sum(0)])
+        for got, want in ((G, (x1 * ww).t() @ x1), (C, (x1 * ww).t() @ y), (A, (xc * ww).t() @ xc), (B, (xc * ww).t() @ yc),
+                          (sums, s1), (sq, (ww * xy * xy).sum(0))):
+            assert float((got[m].double() - want).norm() / want.norm()) < 1e-5, (m, d, Lt, Ls, H, T)
