@@ -196,8 +196,8 @@ cb_status cb_stats_accumulate(cb_plan *plan, const cb_cache *src, const cb_cache
  * lambda * trace(G[m]) / P with CB_LAMBDA_RELATIVE.  D = I by default (the
  * bias row is penalized too); with CB_RIDGE_BIAS_UNPENALIZED the last
  * diagonal entry of D is 0, which equals the paper's centered weighted ridge
- * (weights rescaled to mean one).  G is read in full and must be symmetric
- * (cb_stats_accumulate writes it so).  Blocked Cholesky in fp64, one
+ * (weights rescaled to mean one).  G must be symmetric
+ * (cb_stats_accumulate writes it so); not all of it is read.  Blocked Cholesky in fp64, one
  * workgroup per system.  info[m] = 0 on success, else the 1-based index of the first pivot
  * that is not positive and finite (the column where Cholesky would stop), and
  * maps[m] is zero-filled.  P in {65, 97, 129}, d_t in {64, 96, 128}; wider
