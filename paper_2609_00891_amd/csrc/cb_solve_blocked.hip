@@ -470,6 +470,7 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
     __shared__ double Wl[2][16 * 17], Wk[2][NP * 17];
     __shared__ double red[kWaves][16];
     __shared__ double redh[kWaves];
+    __shared__ int s_info;
     int m, tile;
     if (!item_of(a, a.d_t / 16, m, tile)) return;
     const int tid = threadIdx.x, lane = tid & 63, q = lane & 15, g = lane >> 4;
@@ -478,7 +479,11 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
     double *wm = a.ws + (int64_t)m * a.ws_stride;
     const float *Gm = a.G + (int64_t)(a.m0 + m) * a.P * a.P, *Cm = a.C + (int64_t)(a.m0 + m) * a.P * a.d_t;
     float *Wm = a.maps + (int64_t)(a.m0 + m) * out_rows * a.d_t;
-    bool bad = a.info[a.m0 + m] != 0;
+    // info is read once per workgroup: another workgroup of the system may store the bias pivot's failure while this
+    // one starts, and its waves have to agree (this workgroup finds the same pivot, so either reading serves)
+    if (tid == 0) s_info = __hip_atomic_load(a.info + a.m0 + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    bool bad = s_info != 0;
     double wb = 0.0;                                      // border: this column's bias coefficient
     if (a.border && !bad) {
         // h = M_NN - z . z and (C_N - z . Z) / h with z the bias column's eliminated values
@@ -507,7 +512,7 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
         h = (double)Gm[(int64_t)a.N * a.P + a.N] + (pen ? wm[a.ws_stride - 1] : 0.0) - h;
         bad = !(h > 0.0 && h <= DBL_MAX);                 // the same in every workgroup of the system
         if (bad) {
-            if (tid == 0) a.info[a.m0 + m] = a.N + 1;
+            if (tid == 0) __hip_atomic_store(a.info + a.m0 + m, a.N + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             wb = ((double)Cm[(int64_t)a.N * a.d_t + c] - s) / h;
             if (wave == 0 && g == 0) Wm[(int64_t)a.N * a.d_t + c] = (float)wb;

@@ -278,3 +278,22 @@ def test_stats_shared_targets(cb, d, Lt, Ls, H, T):
         for got, want in ((G, (x1 * ww).t() @ x1), (C, (x1 * ww).t() @ y), (A, (xc * ww).t() @ xc), (B, (xc * ww).t() @ yc),
                           (sums, s1), (sq, (ww * xy * xy).sum(0))):
             assert float((got[m].double() - want).norm() / want.norm()) < 1e-5, (m, d, Lt, Ls, H, T)
+
+
+# Systems that fail at their bias pivot alone (one column past a multiple of 128), many of them between good ones: every
+# workgroup of a failing system writes zeros, whichever of them reports the pivot first.
+@pytest.mark.parametrize("P", [257, 513])
+def test_wide_solve_bias_pivots(cb, P):
+    dt, n = 128, 96
+    G, C = _moments(2, P, dt, P)
+    G[0, -1, -1] = -1.0
+    Gd, Cd = (torch.from_numpy(a).cuda().repeat(n // 2, 1, 1) for a in (G, C))
+    ws = torch.empty(cb.cb_ridge_solve_workspace_bytes(P, dt, n), dtype=torch.uint8, device="cuda")
+    good = None
+    for _ in range(20):
+        maps, info = torch.full_like(Cd, 7.0), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        cb.cb_ridge_solve_ws(Gd, Cd, 1e-3, 0, maps, info, ws)
+        assert info.cpu().tolist() == [P, 0] * (n // 2)
+        assert bool((maps[0::2] == 0).all())
+        good = maps[1].clone() if good is None else good
+        assert bool((maps[1::2] == good).all())
