@@ -515,7 +515,6 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
             if (tid == 0) __hip_atomic_store(a.info + a.m0 + m, a.N + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             wb = ((double)Cm[(int64_t)a.N * a.d_t + c] - s) / h;
-            if (wave == 0 && g == 0) Wm[(int64_t)a.N * a.d_t + c] = (float)wb;
         }
     }
     if (bad) {
@@ -647,6 +646,8 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
         }
         __syncthreads();
     }
+    // (after the barriers above: the caller may solve in place, maps = C, and every wave reads C's last row)
+    if (a.border && wave == 0 && g == 0) Wm[(int64_t)a.N * a.d_t + c] = (float)wb;
     if (sm) {
         // b = mu_y - W^T mu_x (the bias unknown of a border system is a feature like the others here)
         if (a.border && sw != 0.0 && wave == 0 && g == 0) mu_sum = __builtin_fma(sm[1 + a.N] / sw, wb, mu_sum);

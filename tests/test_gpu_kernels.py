@@ -297,3 +297,17 @@ def test_wide_solve_bias_pivots(cb, P):
         assert bool((maps[0::2] == 0).all())
         good = maps[1].clone() if good is None else good
         assert bool((maps[1::2] == good).all())
+
+
+# In place, maps = C: every column of C is read before the coefficients take its place.
+@pytest.mark.parametrize("P", [65, 129, 257, 300, 513])
+def test_solve_in_place(cb, P):
+    dt, n = 128, 40
+    G, C = _moments(2, P, dt, P)
+    Gd, Cd = (torch.from_numpy(a).cuda().repeat(n // 2, 1, 1) for a in (G, C))
+    info = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(cb.cb_ridge_solve_workspace_bytes(P, dt, n), 8), dtype=torch.uint8, device="cuda")
+    maps, both = torch.empty_like(Cd), Cd.clone()
+    cb.cb_ridge_solve_ws(Gd, Cd, 1e-2, REL | UNPEN, maps, info, ws)
+    cb.cb_ridge_solve_ws(Gd, both, 1e-2, REL | UNPEN, both, info, ws)
+    assert torch.equal(maps, both) and bool((info == 0).all())
