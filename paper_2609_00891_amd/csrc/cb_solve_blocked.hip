@@ -18,8 +18,8 @@
 //   update p one workgroup per 128 x 128 tile of the rows below: T -= U_p^T U_p.
 //           The workgroup of the next diagonal tile goes on to factor it, so
 //           that the next panel's solve can start with the next launch;
-//   back    one workgroup per 16 right-hand sides: the substitution from the
-//           last panel up, then the maps.
+//   back    the substitution from the last panel up, then the maps: one
+//           workgroup per 16 right-hand sides, or per system (see the launch).
 // One row and column past a multiple of 128 (P = 128 k + 1, the bias) is no
 // panel of its own: it stays a column like the right-hand sides, and "back"
 // starts with its pivot.
@@ -33,7 +33,9 @@
 // Measured at P = 1025, d_t = 128, a workgroup per system -> now, ms: 16 systems
 // 7.6 -> 0.77, 128 8.6 -> 3.25, 256 9.2 -> 6.3, 512 13.7 -> 12.4, 1,024 27.1 ->
 // 24.4 (26 TFLOP/s; the trailing matrix moves about 33 MB per system); 64 in
-// the fixed scratch 39.6 -> 2.6 (batches of 22 instead of 14).  In "back", a
+// the fixed scratch 39.6 -> 2.6 (batches of 22 instead of 14).  Hundreds of
+// narrower ones, us: P = 161 x 512 457 -> 301, 257 x 512 934 -> 627, 300 x 512
+// 1,171 -> 876, 385 x 1,024 3,570 -> 2,851, 769 x 1,024 14,222 -> 12,551.  In "back", a
 // panel column's operands requested one pair of blocks ahead instead of a whole
 // column: 340 against 195 us for 22 systems.
 //
@@ -57,6 +59,7 @@ namespace {
 constexpr int NB = 8;             // 16-row blocks of a panel
 constexpr int NP = 16 * NB;       // panel rows
 constexpr int DTMAX = 128;
+constexpr int kComputeUnits = 256;
 
 // Geometry of a system and its workspace.  Columns are numbered 0 .. N - 1
 // (the factored part of M), then the d_t right-hand sides, then the bias
@@ -262,6 +265,22 @@ __device__ __forceinline__ void group_columns(const WideArgs &a, int p, int grp,
     }
 }
 
+// The upper blocks of panel p's diagonal tile into LDS (the identity past its nb rows).
+__device__ __forceinline__ void load_diagonal(const WideArgs &a, double *U, double *wm, int p, int tid) {
+    const int nb = panel_rows(a, p);
+#pragma unroll
+    for (int n = 0; n < NB * (NB + 1) / 2 * 256 / kThreads; ++n) {
+        const int e = n * kThreads + tid, b = e >> 8, r = (e >> 4) & 15, c = e & 15;
+        int i = 0;
+#pragma unroll
+        for (int x = 1; x < NB; ++x) i += b >= x * (x + 1) / 2;
+        const int k = b - i * (i + 1) / 2, R = 16 * k + r, Cc = 16 * i + c;
+        const Column x = column_of(a, wm, p, NP * p + min(Cc, nb - 1));
+        const double v = x.p[min(R, nb - 1) * x.rs];
+        U[b * kBS + r * kBR + c] = R < nb && Cc < nb ? v : (R == Cc ? 1.0 : 0.0);
+    }
+}
+
 // U_p,c = U_pp^-T T_p,c for one group of columns; wave w has tile w.
 __global__ __launch_bounds__(kThreads, 4) void wide_solve_kernel(WideArgs a, int p) {
     __shared__ double U[NB * (NB + 1) / 2 * kBS];
@@ -272,7 +291,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_solve_kernel(WideArgs a, int
     const int tid = threadIdx.x, lane = tid & 63, q = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double *wm = a.ws + (int64_t)m * a.ws_stride;
-    const int c0 = NP * p, nb = panel_rows(a, p);
+    const int nb = panel_rows(a, p);
     const bool own = 16 * wave < ncol;
     const int col = min(col0 + 16 * wave + q, col0 + ncol - 1);
     const Column T = column_of(a, wm, p, col);
@@ -292,18 +311,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_solve_kernel(WideArgs a, int
                 for (int e = 0; e < 4; ++e) Z[j][e] = T.p[min(16 * j + 4 * e + g, nb - 1) * T.rs];
         }
     }
-    // U_pp's upper blocks (the identity past its nb rows)
-#pragma unroll
-    for (int n = 0; n < NB * (NB + 1) / 2 * 256 / kThreads; ++n) {
-        const int e = n * kThreads + tid, b = e >> 8, r = (e >> 4) & 15, c = e & 15;
-        int i = 0;
-#pragma unroll
-        for (int x = 1; x < NB; ++x) i += b >= x * (x + 1) / 2;
-        const int k = b - i * (i + 1) / 2, R = 16 * k + r, Cc = 16 * i + c;
-        const Column x = column_of(a, wm, p, c0 + min(Cc, nb - 1));
-        const double v = x.p[min(R, nb - 1) * x.rs];
-        U[b * kBS + r * kBR + c] = R < nb && Cc < nb ? v : (R == Cc ? 1.0 : 0.0);
-    }
+    load_diagonal(a, U, wm, p, tid);
     __syncthreads();
     if (!own) return;
 #pragma unroll
@@ -664,6 +672,143 @@ __global__ __launch_bounds__(kThreads, 2) void wide_back_kernel(WideArgs a) {
     }
 }
 
+// The same back substitution with a system per workgroup: wave w has the 16 right-hand sides 16 w .. + 15 of every
+// panel in its registers, as in wide_solve_kernel, so within a panel there is no barrier, the factor comes past once
+// for all right-hand sides and two workgroups share a compute unit.
+__global__ __launch_bounds__(kThreads, 4) void wide_back_system_kernel(WideArgs a) {
+    __shared__ double U[NB * (NB + 1) / 2 * kBS];
+    __shared__ int s_info;
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, q = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool own = 16 * wave < a.d_t;
+    const int c = 16 * (own ? wave : 0) + q, out_rows = a.csums ? a.P + 1 : a.P, panels = (a.N + NP - 1) / NP;
+    double *wm = a.ws + (int64_t)m * a.ws_stride;
+    float *Wm = a.maps + (int64_t)(a.m0 + m) * out_rows * a.d_t;
+    if (tid == 0) s_info = a.info[a.m0 + m];
+    __syncthreads();
+    bool bad = s_info != 0;
+    double wb = 0.0;                                      // border: this column's bias coefficient
+    if (a.border && !bad) {
+        // h = M_NN - z . z and (C_N - z . Z) / h with z the bias column's eliminated values (N = 128 panels here)
+        double zz = 0.0, zc = 0.0;
+        for (int i = 0; i < panels; ++i) {
+            const Column b = column_of(a, wm, i, a.W - 1), x = column_of(a, wm, i, a.N + c);
+#pragma unroll 8
+            for (int r = g; r < NP; r += 4) {
+                const double z = b.p[r * b.rs];
+                zz = __builtin_fma(z, z, zz);
+                zc = __builtin_fma(z, x.p[r * x.rs], zc);
+            }
+        }
+        for (int o = 16; o < 64; o <<= 1) {
+            zz += __shfl_xor(zz, o);
+            zc += __shfl_xor(zc, o);
+        }
+        const bool pen = a.csums || !(a.flags & CB_RIDGE_BIAS_UNPENALIZED);
+        const double gnn = (double)a.G[((int64_t)(a.m0 + m) * a.P + a.N) * a.P + a.N];
+        const double h = gnn + (pen ? wm[a.ws_stride - 1] : 0.0) - zz;
+        bad = !(h > 0.0 && h <= DBL_MAX);                 // the same in every wave
+        wb = ((double)a.C[((int64_t)(a.m0 + m) * a.P + a.N) * a.d_t + c] - zc) / h;
+        if (bad && tid == 0) a.info[a.m0 + m] = a.N + 1;
+    }
+    if (bad) {
+        for (int e = tid; e < out_rows * a.d_t; e += kThreads) Wm[e] = 0.f;
+        return;
+    }
+    double mu_sum = 0.0;                                  // centered: sum of mu_x,i W_ic over this lane's rows
+    const double *sm = a.csums ? a.csums + (int64_t)(a.m0 + m) * (1 + a.P + a.d_t) : nullptr;
+    const double sw = sm ? sm[0] : 0.0;
+    for (int i = panels - 1; i >= 0; --i) {
+        const int nb = panel_rows(a, i);
+        if (i + 1 < panels) __syncthreads();              // everyone is done with the last panel's U
+        int t = tid;
+        asm volatile("" : "+v"(t));                       // nothing of the panel's addresses is held across the loop
+        load_diagonal(a, U, wm, i, t);
+        asm volatile("" : "+v"(t)::"memory");
+        const Column X = column_of(a, wm, i, a.N + 16 * (own ? wave : 0) + (t & 15));
+        f64x4_t Z[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) Z[j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+        if (own) {
+            // the columns right of the panel (only panels of 128 rows have any), 16 at a time; K step s of a block takes
+            // its columns 4 g + s: 32 consecutive bytes a lane of U, row 4 g + s of this wave's solved right-hand sides
+#pragma unroll 1
+            for (int k0 = NP * (i + 1); k0 < a.N; k0 += 16) {
+                int q = tid & 15, g = (tid >> 4) & 3;
+                asm volatile("" : "+v"(q), "+v"(g));      // addresses are formed here, not held across the loop
+                const int ik = k0 / NP, last = panel_rows(a, ik) - 1;
+                const Column B = column_of(a, wm, ik, a.N + c);
+                const double *S = wm + row_base(a, i) + (int64_t)NP * (k0 - NP * i) + 16 * q + 4 * g;
+                double b[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) b[s] = B.p[min(k0 - NP * ik + 4 * g + s, last) * B.rs];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) b[s] = k0 + 4 * g + s < a.N ? b[s] : 0.0;
+#pragma unroll
+                for (int j0 = 0; j0 < NB; j0 += 4) {
+                    double u[4][4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) u[j][s] = S[256 * (j0 + j) + s];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            Z[j0 + j] = mfma_f64(k0 + 4 * g + s < a.N ? u[j][s] : 0.0, b[s], Z[j0 + j]);
+                }
+            }
+            const Column bias = column_of(a, wm, i, a.W - 1);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                int g = (tid >> 4) & 3;
+                asm volatile("" : "+v"(g)::"memory");     // four rows' loads at a time: registers
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * j + 4 * e + g;
+                    double y = X.p[min(r, nb - 1) * X.rs] - Z[j][e];
+                    if (a.border) y = __builtin_fma(-bias.p[min(r, nb - 1) * bias.rs], wb, y);
+                    Z[j][e] = r < nb ? y : 0.0;
+                }
+            }
+        }
+        __syncthreads();
+        if (!own) continue;
+#pragma unroll
+        for (int j = NB - 1; j >= 0; --j) {
+            if (16 * j >= nb) continue;
+            int q = tid & 15, g = (tid >> 4) & 3;
+            asm volatile("" : "+v"(q), "+v"(g));
+            f64x4_t acc = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k = j + 1; k < NB; ++k)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc = mfma_f64(U[block_of(j, k) * kBS + q * kBR + 4 * s + g], Z[k][s], acc);
+            const f64x4_t y = Z[j] - acc;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) x = mfma_f64(U[block_of(j, j) * kBS + (4 * s + g) * kBR + q], y[s], x);
+            Z[j] = x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 16 * j + 4 * e + g;
+                if (r >= nb) continue;
+                X.p[r * X.rs] = x[e];                     // read by the panels above
+                Wm[(int64_t)(NP * i + r) * a.d_t + c] = (float)x[e];
+                if (sm && sw != 0.0) mu_sum = __builtin_fma(sm[1 + NP * i + r] / sw, x[e], mu_sum);
+            }
+        }
+    }
+    if (!own) return;
+    if (a.border && g == 0) Wm[(int64_t)a.N * a.d_t + c] = (float)wb;
+    if (sm) {
+        // b = mu_y - W^T mu_x (the bias unknown of a border system is a feature like the others here)
+        if (a.border && sw != 0.0 && g == 0) mu_sum = __builtin_fma(sm[1 + a.N] / sw, wb, mu_sum);
+        mu_sum += __shfl_xor(mu_sum, 16);
+        mu_sum += __shfl_xor(mu_sum, 32);
+        if (g == 0) Wm[(int64_t)a.P * a.d_t + c] = (float)((sw != 0.0 ? sm[1 + a.P + c] / sw : 0.0) - mu_sum);
+    }
+}
+
 WideArgs geometry(int32_t P, int32_t d_t) {
     WideArgs a = {};
     a.P = P;
@@ -719,7 +864,14 @@ hipError_t launch_solve_blocked(int32_t n_maps, int32_t P, int32_t d_t, const fl
             if (items > 0)
                 hipLaunchKernelGGL(wide_update_kernel, dim3((unsigned)(n8 * items)), dim3(kThreads), 0, s, a, p, items);
         }
-        hipLaunchKernelGGL(wide_back_kernel, dim3((unsigned)(n8 * (d_t / 16))), dim3(kThreads), 0, s, a);
+        // A system per workgroup where they fill the chip, up to six panels.  Measured, whole solve at d_t = 128,
+        // workgroup per 16 right-hand sides -> per system, us: P = 161 x 512 553 -> 301, 257 x 256 483 -> 360, 300 x
+        // 512 1,243 -> 876, 513 x 256 1,565 -> 1,417, 769 x 256 3,440 -> 3,357; with more panels or fewer systems it
+        // is the chain of one workgroup: 1,025 x 256 6,344 -> 6,400, 257 x 64 179 -> 231, 513 x 64 483 -> 756.
+        if (a.n >= kComputeUnits && panels <= 6)
+            hipLaunchKernelGGL(wide_back_system_kernel, dim3(a.n), dim3(kThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL(wide_back_kernel, dim3((unsigned)(n8 * (d_t / 16))), dim3(kThreads), 0, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -311,3 +311,46 @@ def test_solve_in_place(cb, P):
     cb.cb_ridge_solve_ws(Gd, Cd, 1e-2, REL | UNPEN, maps, info, ws)
     cb.cb_ridge_solve_ws(Gd, both, 1e-2, REL | UNPEN, both, info, ws)
     assert torch.equal(maps, both) and bool((info == 0).all())
+
+
+# Batches that fill the chip: the back substitution takes a system per workgroup (up to six panels) or 16 right-hand
+# sides per workgroup.  Ragged last panels and the bias column, a system that fails inside and one at its bias pivot.
+@pytest.mark.parametrize("n", [255, 256])
+@pytest.mark.parametrize("P,dt", [(130, 64), (161, 128), (257, 96), (300, 128), (769, 64), (770, 64)])
+def test_wide_solve_many_systems(cb, P, dt, n):
+    import oracle
+    G, C = _moments(4, P, dt, P + dt)
+    G[1, P // 2, P // 2] = -1.0
+    G[2, -1, -1] = -1.0
+    W, io = oracle.ridge_solve(G.astype(np.float64), C.astype(np.float64), 1e-3, relative=False)
+    assert io.tolist() == [0, P // 2 + 1, P, 0]
+    Gd, Cd = (torch.from_numpy(a).cuda().repeat(-(-n // 4), 1, 1)[:n].contiguous() for a in (G, C))
+    maps, info = torch.full_like(Cd, 7.0), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(cb.cb_ridge_solve_workspace_bytes(P, dt, n), dtype=torch.uint8, device="cuda")
+    cb.cb_ridge_solve_ws(Gd, Cd, 1e-3, 0, maps, info, ws)
+    assert info.cpu().tolist() == [int(io[m % 4]) for m in range(n)]
+    for k in range(4):
+        assert bool((maps[k::4] == maps[k]).all()), (P, dt, n, k)
+    assert bool((maps[1:3] == 0).all())
+    for k in (0, 3):
+        assert _relF(maps[k].double().cpu().numpy(), W[k]) < 1e-6
+
+
+@pytest.mark.parametrize("dx", [256, 257, 330])
+def test_wide_solve_many_centered(cb, dx):
+    import oracle
+    n, dt = 256, 96
+    G, C = _moments(2, dx, dt, dx)
+    rng = np.random.default_rng(dx)
+    sums = np.concatenate([np.full((2, 1), 50.0), 20 * rng.standard_normal((2, dx + dt))], axis=1)
+    sums[1] = 0.0                                          # no data: means of zero
+    W, io = oracle.ridge_solve_centered(sums, G.astype(np.float64), C.astype(np.float64), 1e-3, relative=True)
+    args = [torch.from_numpy(x).cuda().repeat(n // 2, *[1] * (x.ndim - 1)) for x in (sums, G, C)]
+    ws = torch.empty(cb.cb_ridge_solve_workspace_bytes(dx, dt, n), dtype=torch.uint8, device="cuda")
+    maps = torch.full((n, dx + 1, dt), 7.0, device="cuda")
+    info = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cb.cb_ridge_solve_centered_ws(*args, 1e-3, REL, maps, info, ws)
+    assert (info.cpu().numpy() == 0).all() and (io == 0).all()
+    for m in range(2):
+        assert bool((maps[m::2] == maps[m]).all())
+        assert _relF(maps[m].double().cpu().numpy(), W[m]) < 1e-6
