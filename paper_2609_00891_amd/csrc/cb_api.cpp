@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "cb_internal.h"
+#include "cb_rules.h"
 
 struct cb_plan {
     int device = 0;
@@ -51,6 +52,7 @@ struct cb_plan {
     // application schedule
     int32_t n_groups = 0;
     cb::ApplyGroup *d_groups = nullptr;
+    int32_t apply_resident[9] = {};   // workgroups per compute unit, [target rotation][source rotation]
     // multi-layer application: split coefficients
     uint16_t *d_whi = nullptr;
     float *d_bias = nullptr;
@@ -557,6 +559,7 @@ cb_status cb_plan_create(const cb_head_map *map, const cb_cache *src_geom, const
         }
     }
     p->n_groups = (int)agroups.size();
+    cb::apply_residents(d_s, d_t, p->apply_resident);
 
     // ---- device allocations
     const int64_t slot_floats = cb::stats_slot_floats(d_s, d_t);
@@ -1525,28 +1528,10 @@ static cb_status apply_single(cb_plan *p, const float *maps, const cb_cache *src
     a.os = strides_of(tgt_out);
     a.T = cb::make_fastdiv((uint32_t)src->seq_len);
     a.N = (int32_t)N;
-    // Token tiles of whole 32-token sub-blocks, at most 8192 tokens.  One
-    // workgroup runs per compute unit, and loading its maps and filling its
-    // ring costs about as much as kFixed sub-blocks; so the count of tiles per
-    // source block that makes the fewest rounds times (sub-blocks + kFixed)
-    // is taken (kFixed = 4 measured the same or slower).  Measured, 1,024 maps
-    // (640 source blocks), tiles of at least 256 tokens and about 16 workgroups
-    // per compute unit, after a pass that split the maps -> now, us: 32 tokens
-    // 114 -> 22, 200 135 -> 43, 777 260 -> 114, 3,000 510 -> 355, 8,000 962 ->
-    // 817; 320 maps of 96 and 128, 777 tokens 70 -> 32.
-    {
-        constexpr int64_t kFixed = 8;
-        const int64_t sub = (N + 31) / 32, fewest = (sub + 255) / 256;
-        int64_t best = -1, per = sub;
-        for (int64_t nt = fewest; nt <= std::min(sub, fewest + 31); ++nt) {
-            const int64_t ct = (sub + nt - 1) / nt;
-            const int64_t rounds = ((int64_t)p->n_groups * ((sub + ct - 1) / ct) + p->n_cu - 1) / p->n_cu;
-            if (best >= 0 && rounds * (ct + kFixed) >= best) continue;
-            best = rounds * (ct + kFixed);
-            per = ct;
-        }
-        a.tile_tokens = (int32_t)(32 * per);
-    }
+    const int rs = tgt_rope ? 1 + (tgt_rope->style != 0) : 0, sr = src_rope ? 1 + (src_rope->style != 0) : 0;
+    a.tile_tokens = (int32_t)(32 * cb::choose_apply_sub_blocks((N + 31) / 32, p->n_groups, p->n_cu,
+                                                               p->apply_resident[3 * rs + sr],
+                                                               64 * (p->d_s + (int64_t)p->n_maps * p->d_t / p->n_groups)));
     a.n_tiles = (int32_t)((N + a.tile_tokens - 1) / a.tile_tokens);
     a.groups = p->d_groups;
     a.maps = maps;

@@ -550,7 +550,37 @@ hipError_t launch_apply_t(int n_groups, const ApplyArgs &a, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+template <int DS, int DT, int SR>
+void residents_sr(int32_t *out) {
+    auto count = [](auto kernel) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, ACfg<DS, DT>::NT, 0) != hipSuccess)
+            (void)hipGetLastError();
+        return n > 0 ? n : 1;
+    };
+    out[0 + SR] = count(apply_kernel<DS, DT, kRopeNone, SR>);
+    out[3 + SR] = count(apply_kernel<DS, DT, kRopeHalf, SR>);
+    out[6 + SR] = count(apply_kernel<DS, DT, kRopeInterleaved, SR>);
+}
+
+template <int DS, int DT>
+hipError_t residents_t(int32_t *out) {
+    residents_sr<DS, DT, 0>(out);
+    if constexpr (DS == 64 || DS == 128) {
+        residents_sr<DS, DT, 1>(out);
+        residents_sr<DS, DT, 2>(out);
+    }
+    return hipSuccess;
+}
+
+hipError_t residents(int d_s, int d_t, int32_t *out) { CB_DISPATCH(residents_t, d_s, d_t, out); }
+
 }  // namespace
+
+void apply_residents(int d_s, int d_t, int32_t out[9]) {
+    for (int i = 0; i < 9; ++i) out[i] = 1;
+    (void)residents(d_s, d_t, out);
+}
 
 #define CB_DISPATCH_APPLY(d_s, d_t, ...)                                     \
     switch ((d_s) * 1000 + (d_t)) {                                          \

@@ -276,6 +276,8 @@ hipError_t launch_solve_blocked_static(int32_t n_maps, int32_t P, int32_t d_t, c
 hipError_t launch_solve(int32_t n_maps, int32_t P, int32_t d_t, const float *G, const float *C,
                         float lambda, uint32_t flags, float *maps, int32_t *info, hipStream_t s);
 hipError_t launch_apply(int d_s, int d_t, int n_groups, const ApplyArgs &a, hipStream_t s);
+// Workgroups of the application kernel that one compute unit holds, [3 (target rotation style + 1) + source style + 1].
+void apply_residents(int d_s, int d_t, int32_t out[9]);
 
 // Geometry of the statistics kernel, shared with the host for workspace sizing.
 constexpr int kStatsTileTokens = 32;
