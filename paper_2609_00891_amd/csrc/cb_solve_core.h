@@ -24,21 +24,42 @@ __device__ __forceinline__ f64x4_t mfma_f64(double a, double b, f64x4_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// acc += (lane R of this row of 16 lanes' a) * b.  a was final several
-// instructions earlier (b is computed from a later value), which covers the
-// two wait states a DPP read needs after a VALU write.
-template <int R>
-__device__ __forceinline__ void fmac_row_bcast(double &acc, double a, double b) {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(R));
+// DPP reads.  A register written by a vector instruction may be read through
+// DPP two wait states later at the earliest, and the compiler does not see that
+// an inline statement reads through DPP: each of them opens with the wait itself.
+
+// t[i] += (lane R + i of this row of 16 lanes' a) * nt and v[i] += (the same) * nv, i < ROWS.
+template <int R, int ROWS>
+__device__ __forceinline__ void fmac_rows_bcast(double *t, double *v, double a, double nt, double nv) {
+#define CB_FMAC(d, x, i) "v_fmac_f64_dpp %[" #d #i "], %[a], %[" #x "] row_newbcast:%[r" #i "] row_mask:0xf bank_mask:0xf\n\t"
+#define CB_ROW(i) CB_FMAC(t, nt, i) CB_FMAC(v, nv, i)
+#define CB_OUT(i) [t##i] "+&v"(t[i]), [v##i] "+&v"(v[i])
+#define CB_IN [a] "v"(a), [nt] "v"(nt), [nv] "v"(nv)
+#define CB_LANE(i) [r##i] "n"(R + i)
+    static_assert(ROWS >= 1 && ROWS <= 4 && R + ROWS <= 16, "one to four rows");
+    if constexpr (ROWS == 1)
+        asm("s_nop 1\n\t" CB_ROW(0) : CB_OUT(0) : CB_IN, CB_LANE(0));
+    else if constexpr (ROWS == 2)
+        asm("s_nop 1\n\t" CB_ROW(0) CB_ROW(1) : CB_OUT(0), CB_OUT(1) : CB_IN, CB_LANE(0), CB_LANE(1));
+    else if constexpr (ROWS == 3)
+        asm("s_nop 1\n\t" CB_ROW(0) CB_ROW(1) CB_ROW(2)
+            : CB_OUT(0), CB_OUT(1), CB_OUT(2) : CB_IN, CB_LANE(0), CB_LANE(1), CB_LANE(2));
+    else
+        asm("s_nop 1\n\t" CB_ROW(0) CB_ROW(1) CB_ROW(2) CB_ROW(3)
+            : CB_OUT(0), CB_OUT(1), CB_OUT(2), CB_OUT(3) : CB_IN, CB_LANE(0), CB_LANE(1), CB_LANE(2), CB_LANE(3));
+#undef CB_FMAC
+#undef CB_ROW
+#undef CB_OUT
+#undef CB_IN
+#undef CB_LANE
 }
 
 // Lane R of this row of 16 lanes' v.
 template <int R>
 __device__ __forceinline__ double row_bcast(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)u, 0x150 + R, 0xf, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(u >> 32), 0x150 + R, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    double o;
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=&v"(o) : "v"(v), "n"(R));
+    return o;
 }
 
 // 1 / d: the hardware estimate y and 1 / (1 - r) = 1 + r + r^2 with r = 1 - d y.
@@ -48,12 +69,13 @@ __device__ __forceinline__ double rcp_f64(double d) {
     return __builtin_fma(y, __builtin_fma(r, r, r), y);
 }
 
+// Rows R .. 15, up to a multiple of four, then four at a time.
 template <int K, int R>
 __device__ __forceinline__ void pivot_rows(double (&t)[16], double (&v)[16], double nt, double nv) {
     if constexpr (R < 16) {
-        fmac_row_bcast<R>(t[R], t[K], nt);
-        fmac_row_bcast<R>(v[R], t[K], nv);
-        pivot_rows<K, R + 1>(t, v, nt, nv);
+        constexpr int ROWS = 4 - R % 4;
+        fmac_rows_bcast<R, ROWS>(t + R, v + R, t[K], nt, nv);
+        pivot_rows<K, R + ROWS>(t, v, nt, nv);
     }
 }
 

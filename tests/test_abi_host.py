@@ -309,3 +309,24 @@ def test_bindings_check_output_sizes_against_the_plan():
         cb.cb_stats_means(plan, src, src, z32(4, 16)[:, 1:], z64(4, 513), w_row_stride=16)    # 63 < 64 values
     with pytest.raises(ValueError, match="weights"):
         cb.cb_stats_means(plan, src, src, z32(16, 4).t(), z64(4, 513), w_row_stride=16)   # strided rows
+
+
+def test_inline_dpp_reads_open_with_their_wait():
+    # a DPP read has to come two wait states after a vector write of its operand, and the compiler does not look into
+    # inline assembly: every such statement starts with the wait
+    import glob
+    csrc = os.path.join(ROOT, "paper_2609_00891_amd", "csrc")
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(csrc, "*"))):
+        text = open(path).read()
+        text = re.sub(r"//[^\n]*", "", text)
+        macros = dict(re.findall(r"#define (\w+)(?:\([^)]*\))? ((?:[^\n]|\\\n)*)", text))
+        dpp = {m for m, body in macros.items() if "_dpp " in body}
+        dpp |= {m for m, body in macros.items() if any(re.search(rf"\b{d}\b", body) for d in dpp)}
+        body = re.sub(r"#define (?:[^\n]|\\\n)*", "", text)
+        for stmt in re.findall(r"\basm\s*(?:volatile)?\s*\((.*?)\)\s*;", body, flags=re.S):
+            code = stmt.split(" : ")[0].split("\n            :")[0]
+            if "_dpp " in code or any(re.search(rf"\b{m}\(", code) for m in dpp):
+                seen += 1
+                assert code.lstrip().startswith('"s_nop 1'), (os.path.basename(path), code)
+    assert seen >= 2
