@@ -32,11 +32,15 @@
 //     pivot step is one v_fmac with a row broadcast (DPP) per row and column;
 //   * 36 upper blocks of 16 x 17 doubles are 78 KB of LDS at d_s = 128 and a
 //     lane has 128 registers, so two systems share a compute unit and one's
-//     pivots overlap the other's products.
+//     pivots overlap the other's products.  (At d_t = 128 two to four values
+//     spill, elsewhere none: the bias coefficient is taken out of a row of
+//     right-hand sides where the back substitution reaches it.  Out of all rows
+//     in a pass before, 30 spilled at d_s = d_t = 128 and 250 at d_t = 64 and 96:
+//     1,024 systems 150 -> 146, 154 -> 121 and 120 -> 100 us.)
 // Measured, before (Gauss-Jordan in registers, one barrier per pivot) and now,
-// us: 1,024 systems of d_s = d_t = 128 942 -> 150 (MFMA floor 70); 320 centered
+// us: 1,024 systems of d_s = d_t = 128 942 -> 146 (MFMA floor 70); 320 centered
 // ones of 96 and 128 307 -> 45; 10,240 centered ones of 128 and 128 8,960 ->
-// 1,400; 4 systems of 64 and 64 97 -> 14.  With a fifth wave factoring beside
+// 1,400; 4 systems of 64 and 64 97 -> 15.  With a fifth wave factoring beside
 // four that own two tiles (168 registers, one system per compute unit) 245; the
 // same with broadcasts by v_readlane 250.
 //
@@ -295,25 +299,21 @@ __global__ __launch_bounds__(kThreads, 4) void ridge_solve_kernel(const float *_
         return;
     }
     if (!owner) return;
-    // plain: the bias unknown, W_N = (C_N - z_g . Z) / h, taken out of the right-hand sides
+    // plain: the bias unknown, W_N = (C_N - z_g . Z) / h, taken out of the right-hand sides as each row is solved
+    double wb = 0.0;
     if constexpr (!CENTERED) {
         f64x4_t s4 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            asm volatile("" ::: "memory");                // z_g is read where it is used, not held in registers
+            int g = (tid >> 4) & 3;
+            asm volatile("" : "+v"(g)::"memory");         // z_g is read where it is used, not held in registers
 #pragma unroll
             for (int e = 0; e < 4; ++e) s4[e] = __builtin_fma(zg[16 * j + 4 * e + g], Z[j][e], s4[e]);
         }
         double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
         s += __shfl_xor(s, 16);
         s += __shfl_xor(s, 32);
-        const double wb = ((double)Cm[N * d_t + col] - s) * s_h;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int e = 0; e < 4; ++e) Z[j][e] = __builtin_fma(-zg[16 * j + 4 * e + g], wb, Z[j][e]);
-        }
+        wb = ((double)Cm[N * d_t + col] - s) * s_h;
         if (g == 0) Wm[N * d_t + col] = (float)wb;
     }
     // back substitution: every wave for its own columns, no barrier
@@ -329,7 +329,11 @@ __global__ __launch_bounds__(kThreads, 4) void ridge_solve_kernel(const float *_
         for (int k = i + 1; k < NB; ++k)
 #pragma unroll
             for (int s = 0; s < 4; ++s) acc = mfma_f64(U[block_of(i, k) * kBS + q * kBR + 4 * s + g], Z[k][s], acc);
-        const f64x4_t y = Z[i] - acc;
+        f64x4_t y = Z[i] - acc;
+        if constexpr (!CENTERED) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = __builtin_fma(-zg[16 * i + 4 * e + g], wb, y[e]);
+        }
 #pragma unroll
         for (int s = 0; s < 4; ++s) x = mfma_f64(v[s], y[s], x);
         Z[i] = x;
