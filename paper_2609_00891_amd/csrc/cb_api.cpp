@@ -82,66 +82,6 @@ cb_status ok() {
 
 bool supported_width(int d) { return d == 64 || d == 96 || d == 128; }
 
-// Work units of a call: each item's token tiles (KT tokens of one sequence)
-// are cut into n_chunks chunks of chunk_tiles tiles.  Enough (item, chunk)
-// units to give every compute unit `per_cu` of them, at most 2048 tiles (64Ki
-// tokens) per fp32 partial, and never more chunks than the plan's workspace
-// holds (max_chunks <= 0: no such limit).
-void choose_chunks(int64_t tiles, int n_items, int n_cu, int max_chunks, int *n_chunks, int *chunk_tiles,
-                   int per_cu = 8) {
-    if (tiles <= 0) {
-        *n_chunks = 0;
-        *chunk_tiles = 1;
-        return;
-    }
-    const int64_t target_units = (int64_t)per_cu * n_cu;
-    int64_t nc = (target_units + n_items - 1) / n_items;
-    nc = std::max<int64_t>(nc, (tiles + 2047) / 2048);
-    nc = std::min<int64_t>(nc, tiles);
-    if (max_chunks > 0) nc = std::min<int64_t>(nc, max_chunks);
-    nc = std::max<int64_t>(nc, 1);
-    const int64_t ct = (tiles + nc - 1) / nc;
-    *chunk_tiles = (int)ct;
-    *n_chunks = (int)((tiles + ct - 1) / ct);
-}
-
-// The moments' chunks.  One workgroup runs per compute unit, so a call takes
-// about ceil(units / compute units) rounds of a chunk's tiles plus a fixed part
-// (ring fill and drain, about 5 tiles' time), and every unit's partial is written
-// and read again: `unit_tiles` times the bytes of a tile.  The cheapest count is
-// taken among those whose fp32 partials run over at most a quarter more tiles
-// than eight units per compute unit give; for the uncentered moments, whose error
-// is that of the weight's split, over up to 64 tiles.  (At 64 tiles in place of
-// 16 their maps are 2.3e-6 from 64 bits as before; centered ones over 96 tiles in
-// place of 23 went from 1.5e-6 to 3.7e-6.)
-// Measured, kernel + reduction, eight units per compute unit -> this rule, us:
-// 1,024 maps of 128 and 128, one 2,048-token sequence, 280 + 234 (4 chunks per
-// item) -> 236 + 83 (1); 320 centered maps of 96 and 128, 6 x 1,531 tokens, 435 +
-// 121 (13) -> 439 + 70 (11); 4 maps of 64 and 64, 4 x 256 tokens, 6 + 34 (32) -> 6 + 7 (16).
-void choose_stats_chunks(int64_t tiles, int n_items, int n_cu, int max_chunks, int d_s, int d_t, bool centered,
-                         int *n_chunks, int *chunk_tiles) {
-    choose_chunks(tiles, n_items, n_cu, 0, n_chunks, chunk_tiles);
-    if (*n_chunks <= 1) return;
-    const int64_t longest = std::max<int64_t>(centered ? 0 : 64, *chunk_tiles + *chunk_tiles / 4);
-    int64_t most = std::min<int64_t>(tiles, (int64_t)*n_chunks * 3 / 2);
-    if (max_chunks > 0) most = std::min<int64_t>(most, max_chunks);
-    const double unit_tiles = 16.0 * (double)cb::stats_slot_floats(d_s, d_t) /
-                              (double)(cb::kStatsTileTokens * 2 * (d_s + 2 * d_t));
-    double best = -1.0;
-    for (int64_t nc = 1; nc <= most; ++nc) {
-        const int64_t ct = (tiles + nc - 1) / nc;
-        if ((ct > longest && nc < most) || (tiles + ct - 1) / ct != nc) continue;
-        const int64_t units = nc * n_items;
-        const double cost = (double)((units + n_cu - 1) / n_cu) * (double)(ct + 5) + (double)units * unit_tiles / n_cu;
-        if (best < 0.0 || cost < best) {
-            best = cost;
-            *n_chunks = (int)nc;
-            *chunk_tiles = (int)ct;
-        }
-    }
-    if (best < 0.0) choose_chunks(tiles, n_items, n_cu, max_chunks, n_chunks, chunk_tiles);
-}
-
 cb_status check_device(const cb_plan *p) {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return fail(CB_ERR_DEVICE, "hipGetDevice failed");
@@ -182,10 +122,15 @@ int32_t units_per_xcd(const cb_plan *p, int n_chunks) {
 
 cb::Strides strides_of(const cb_cache *c) { return {c->s_layer, c->s_kv, c->s_seq, c->s_head, c->s_tok}; }
 
+// Bytes that a work unit's partial costs, written once and read once for two maps, in tiles of an item of two.
+double partial_tiles(int d_s, int d_t) {
+    return 16.0 * (double)cb::stats_slot_floats(d_s, d_t) / (double)(cb::kStatsTileTokens * 2 * (d_s + 2 * d_t));
+}
+
 // Validation and work units shared by the statistics calls.  *empty is set
 // for a call without tokens (nothing to enqueue).
 cb_status prepare_stats(const cb_plan *p, const cb_cache *src, const cb_cache *tgt, const float *weights,
-                        int64_t w_row_stride, cb::StatsArgs &a, bool &empty, bool centered = false) {
+                        int64_t w_row_stride, cb::StatsArgs &a, bool &empty) {
     if (cb_status s = check_cache("src", src, p->L_s, p->H_s, p->d_s)) return s;
     if (cb_status s = check_cache("tgt", tgt, p->L_t, p->H_t, p->d_t)) return s;
     if (src->n_seqs != tgt->n_seqs || src->seq_len != tgt->seq_len)
@@ -216,8 +161,8 @@ cb_status prepare_stats(const cb_plan *p, const cb_cache *src, const cb_cache *t
     a.seq_len = (uint32_t)src->seq_len;
     a.TPS = cb::make_fastdiv((uint32_t)tps);
     a.n_tiles = (int32_t)tiles;
-    choose_stats_chunks(tiles, p->n_items, p->n_cu, p->max_chunks, p->d_s, p->d_t, centered, &a.n_chunks,
-                        &a.chunk_tiles);
+    cb::choose_stats_chunks(tiles, p->n_items, p->n_cu, p->max_chunks, partial_tiles(p->d_s, p->d_t), &a.n_chunks,
+                            &a.chunk_tiles);
     if (a.n_chunks > p->max_chunks) return fail(CB_ERR_UNSUPPORTED, "internal: chunk count exceeds workspace");
     a.n_items = p->n_items;
     a.per_xcd = units_per_xcd(p, a.n_chunks);
@@ -533,12 +478,10 @@ cb_status cb_plan_create(const cb_head_map *map, const cb_cache *src_geom, const
     int nc = 1, ct = 1;
     const int64_t KT = cb::kStatsTileTokens;
     // (a call's tiles may be fewer than the plan's or, with short sequences, more than its tokens / KT: the most
-    // chunks that any size up to the largest would take)
+    // chunks among the plan's tiles, half of them, a quarter, ...; a call that would take more is held to it)
     for (int64_t t = (std::max<int64_t>(max_tokens_per_call, 1) + KT - 1) / KT; t >= 1; t /= 2) {
-        for (bool centered : {false, true}) {
-            choose_stats_chunks(t, p->n_items, p->n_cu, 0, d_s, d_t, centered, &nc, &ct);
-            p->max_chunks = std::max(p->max_chunks, nc);
-        }
+        cb::choose_stats_chunks(t, p->n_items, p->n_cu, 0, partial_tiles(d_s, d_t), &nc, &ct);
+        p->max_chunks = std::max(p->max_chunks, nc);
     }
 
     std::vector<cb::ApplyGroup> agroups;
@@ -1098,8 +1041,8 @@ cb_status cb_stats_means(cb_plan *p, const cb_cache *src, const cb_cache *tgt, c
     {
         const int64_t ne = 1 + p->d_s + p->d_t + (sq ? p->d_s + p->d_t : 0);
         const int64_t cap = (int64_t)p->max_chunks * cb::stats_slot_floats(p->d_s, p->d_t) / (2 * ne);
-        choose_chunks(a.n_tiles, p->n_items, p->n_cu, (int)std::min<int64_t>(cap, 1 << 20), &a.n_chunks,
-                      &a.chunk_tiles, 16);
+        cb::choose_chunks(a.n_tiles, p->n_items, p->n_cu, (int)std::min<int64_t>(cap, 1 << 20), &a.n_chunks,
+                          &a.chunk_tiles, 16);
         a.per_xcd = units_per_xcd(p, a.n_chunks);
     }
     if (cb::launch_means(p->d_s, p->d_t, a, sq != nullptr, st) != hipSuccess)
@@ -1132,7 +1075,7 @@ cb_status cb_stats_accumulate_centered(cb_plan *p, const cb_cache *src, const cb
     }
     cb::StatsArgs a = {};
     bool empty = false;
-    if (cb_status s = prepare_stats(p, src, tgt, weights, w_row_stride, a, empty, true)) return s;
+    if (cb_status s = prepare_stats(p, src, tgt, weights, w_row_stride, a, empty)) return s;
     if (empty) return ok();
     a.sums = sums;
     hipStream_t st = (hipStream_t)stream;
@@ -1173,7 +1116,7 @@ cb_status cb_stats_accumulate_shifted(cb_plan *p, const cb_cache *src, const cb_
     }
     cb::StatsArgs a = {};
     bool empty = false;
-    if (cb_status s = prepare_stats(p, src, tgt, weights, w_row_stride, a, empty, true)) return s;
+    if (cb_status s = prepare_stats(p, src, tgt, weights, w_row_stride, a, empty)) return s;
     if (empty) return ok();
     a.sums = shift;
     a.bias_sums = 1;

@@ -6,6 +6,70 @@
 
 namespace cb {
 
+// Work units of a call: each item's token tiles (KT tokens of one sequence)
+// are cut into n_chunks chunks of chunk_tiles tiles.  Enough (item, chunk)
+// units to give every compute unit `per_cu` of them, at most 2048 tiles (64Ki
+// tokens) per fp32 partial, and never more chunks than the plan's workspace
+// holds (max_chunks <= 0: no such limit).
+inline void choose_chunks(int64_t tiles, int n_items, int n_cu, int max_chunks, int *n_chunks, int *chunk_tiles,
+                          int per_cu = 8) {
+    if (tiles <= 0) {
+        *n_chunks = 0;
+        *chunk_tiles = 1;
+        return;
+    }
+    const int64_t target_units = (int64_t)per_cu * n_cu;
+    int64_t nc = (target_units + n_items - 1) / n_items;
+    nc = std::max<int64_t>(nc, (tiles + 2047) / 2048);
+    nc = std::min<int64_t>(nc, tiles);
+    if (max_chunks > 0) nc = std::min<int64_t>(nc, max_chunks);
+    nc = std::max<int64_t>(nc, 1);
+    const int64_t ct = (tiles + nc - 1) / nc;
+    *chunk_tiles = (int)ct;
+    *n_chunks = (int)((tiles + ct - 1) / ct);
+}
+
+// Squared rounding error that `tiles` tiles summed in chunks of ct leave in a
+// moment of slowly growing sums, in units of the last place of the result: a
+// tile adds four products to the chunk's fp32 sum, which grows to ct / tiles of
+// the whole, and every chunk is one addition to the whole.
+inline double stats_error2(int64_t tiles, int64_t ct) {
+    return 4.0 * (double)ct * (double)ct / (3.0 * (double)tiles) + (double)tiles / (3.0 * (double)ct);
+}
+
+// The moments' chunks.  One workgroup runs per compute unit, so a call takes
+// about ceil(units / compute units) rounds of a chunk's tiles plus a fixed part
+// (ring fill and drain, about 5 tiles' time), and every unit's partial is written
+// and read again, `unit_tiles` tiles' bytes.  The cheapest count is taken among
+// those whose sums are as precise as those of eight units per compute unit
+// (stats_error2), and no longer than 2048 tiles.  Many short chunks may grow and
+// stay as precise; long ones may not: 1,024 maps over one 2,048-token sequence
+// keep 4 chunks of 16 tiles (540 us a call, G 2.5e-7 from 64 bits; one chunk of 64
+// took 335 us and left 4.0e-7, and sums of 16 tiles that a chunk of 64 adds to its
+// partial in memory take 500: it is the partials' traffic).
+// Measured, one call, eight units per compute unit -> this rule, us: 128 maps of
+// 128 and 128, 4 x 2,048 tokens 380 -> 181 (32 chunks per item -> 8), about means
+// 417 -> 185; 4 maps of 64 and 64, 4 x 256 tokens 40 -> 17 (32 -> 16), about means
+// 53 -> 19; two maps of 128 and 128, 65,536 tokens 3,120 -> 113 (2,048 -> 171).
+inline void choose_stats_chunks(int64_t tiles, int n_items, int n_cu, int max_chunks, double unit_tiles, int *n_chunks,
+                                int *chunk_tiles) {
+    choose_chunks(tiles, n_items, n_cu, max_chunks, n_chunks, chunk_tiles);
+    const int64_t most = std::min<int64_t>({tiles, (int64_t)*n_chunks + *n_chunks / 8, max_chunks > 0 ? max_chunks : tiles});
+    const double limit = stats_error2(tiles, *chunk_tiles);
+    double best = -1.0;
+    for (int64_t nc = 1, ct = tiles, next; ct > 0 && nc <= most; nc = next) {
+        ct = (tiles + nc - 1) / nc;
+        next = ct > 1 ? (tiles + ct - 2) / (ct - 1) : most + 1;     // the first count with shorter chunks
+        if (ct > 2048 || stats_error2(tiles, ct) > limit) continue;
+        const int64_t units = nc * n_items;
+        const double cost = (double)((units + n_cu - 1) / n_cu) * (double)(ct + 5) + (double)units * unit_tiles / n_cu;
+        if (best >= 0.0 && cost >= best) continue;
+        best = cost;
+        *n_chunks = (int)nc;
+        *chunk_tiles = (int)ct;
+    }
+}
+
 // Token tiles of the single-layer application, in 32-token sub-blocks: a
 // source block's `sub` sub-blocks go to workgroups of the returned count each,
 // at most 256 (8192 tokens).  A compute unit holds `resident` workgroups.

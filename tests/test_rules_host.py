@@ -12,6 +12,13 @@ extern "C" {
 int64_t apply_sub_blocks(int64_t sub, int64_t groups, int64_t n_cu, int64_t resident, int64_t bytes) {
     return cb::choose_apply_sub_blocks(sub, groups, n_cu, resident, bytes);
 }
+void stats_chunks(int64_t tiles, int items, int n_cu, int most, double unit_tiles, int *nc, int *ct) {
+    cb::choose_stats_chunks(tiles, items, n_cu, most, unit_tiles, nc, ct);
+}
+void even_chunks(int64_t tiles, int items, int n_cu, int *nc, int *ct) {
+    cb::choose_chunks(tiles, items, n_cu, 0, nc, ct);
+}
+double stats_error2(int64_t tiles, int64_t ct) { return cb::stats_error2(tiles, ct); }
 double apply_cost(int64_t sub, int64_t per, int64_t groups, int64_t n_cu, int64_t resident, double rate) {
     return cb::apply_cost(sub, per, groups, n_cu, resident, rate);
 }
@@ -29,7 +36,34 @@ def rules(tmp_path_factory):
     i64 = ctypes.c_int64
     lib.apply_sub_blocks.argtypes, lib.apply_sub_blocks.restype = [i64] * 5, i64
     lib.apply_cost.argtypes, lib.apply_cost.restype = [i64] * 5 + [ctypes.c_double], ctypes.c_double
+    ip = ctypes.POINTER(ctypes.c_int)
+    lib.stats_chunks.argtypes = [i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_double, ip, ip]
+    lib.even_chunks.argtypes = [i64, ctypes.c_int, ctypes.c_int, ip, ip]
+    lib.stats_error2.argtypes, lib.stats_error2.restype = [i64, i64], ctypes.c_double
     return lib
+
+
+def _chunks(f, *args):
+    nc, ct = ctypes.c_int(-1), ctypes.c_int(-1)
+    f(*args, ctypes.byref(nc), ctypes.byref(ct))
+    return nc.value, ct.value
+
+
+# Chunks of the moments: they cover the tiles, an fp32 sum runs over at most 2048 tiles and its error is at most that of
+# eight units per compute unit.
+@pytest.mark.parametrize("unit_tiles", [5.3, 10.0, 35.3])
+@pytest.mark.parametrize("items", [1, 2, 6, 64, 76, 160, 161, 320, 512, 640, 2049, 5120])
+def test_stats_chunks_hold_their_bounds(rules, items, unit_tiles):
+    for limit in [1, 31, 33, 500, 1030, 6400, 38936, 70000]:
+        sizes = sorted({t for k in range(1, 60) for t in (limit * k // 59, limit // k)} | {1, limit}) if limit > 600 else \
+            range(1, limit + 1)
+        for tiles in sizes:
+            if tiles < 1:
+                continue
+            nc, ct = _chunks(rules.stats_chunks, tiles, items, 256, 0, unit_tiles)
+            n0, ct0 = _chunks(rules.even_chunks, tiles, items, 256)
+            assert 1 <= nc and (nc - 1) * ct < tiles <= nc * ct and ct <= 2048, (tiles, limit, nc, ct)
+            assert rules.stats_error2(tiles, ct) <= rules.stats_error2(tiles, ct0), (tiles, limit, nc, ct, ct0)
 
 
 # Application tiles: the chosen one costs at most 10% more than the best of all, and at most 5% more than tiles of at least
