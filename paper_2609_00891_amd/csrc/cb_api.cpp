@@ -475,14 +475,8 @@ cb_status cb_plan_create(const cb_head_map *map, const cb_cache *src_geom, const
             map_item[items[i].map[s]] = i;
             map_slot[items[i].map[s]] = s;
         }
-    int nc = 1, ct = 1;
-    const int64_t KT = cb::kStatsTileTokens;
-    // (a call's tiles may be fewer than the plan's or, with short sequences, more than its tokens / KT: the most
-    // chunks among the plan's tiles, half of them, a quarter, ...; a call that would take more is held to it)
-    for (int64_t t = (std::max<int64_t>(max_tokens_per_call, 1) + KT - 1) / KT; t >= 1; t /= 2) {
-        cb::choose_stats_chunks(t, p->n_items, p->n_cu, 0, partial_tiles(d_s, d_t), &nc, &ct);
-        p->max_chunks = std::max(p->max_chunks, nc);
-    }
+    p->max_chunks = cb::most_stats_chunks((std::max<int64_t>(max_tokens_per_call, 1) + cb::kStatsTileTokens - 1) /
+                                              cb::kStatsTileTokens, p->n_items, p->n_cu);
 
     std::vector<cb::ApplyGroup> agroups;
     for (const auto &g : groups) {

@@ -70,6 +70,15 @@ inline void choose_stats_chunks(int64_t tiles, int n_items, int n_cu, int max_ch
     }
 }
 
+// The most chunks that choose_stats_chunks takes for any call of up to `tiles`
+// tiles (its count grows with the tiles, but for rounding).  Calls of many short
+// sequences can have more tiles than the plan's tokens fill; they are held to it.
+inline int32_t most_stats_chunks(int64_t tiles, int n_items, int n_cu) {
+    const int64_t per_cu8 = (8LL * n_cu + n_items - 1) / n_items;
+    const int64_t nc = std::min(tiles, std::max(per_cu8, (tiles + 2047) / 2048));
+    return (int32_t)std::min(tiles, nc + nc / 8);
+}
+
 // Token tiles of the single-layer application, in 32-token sub-blocks: a
 // source block's `sub` sub-blocks go to workgroups of the returned count each,
 // at most 256 (8192 tokens).  A compute unit holds `resident` workgroups.

@@ -18,6 +18,7 @@ void stats_chunks(int64_t tiles, int items, int n_cu, int most, double unit_tile
 void even_chunks(int64_t tiles, int items, int n_cu, int *nc, int *ct) {
     cb::choose_chunks(tiles, items, n_cu, 0, nc, ct);
 }
+int most_chunks(int64_t tiles, int items, int n_cu) { return cb::most_stats_chunks(tiles, items, n_cu); }
 double stats_error2(int64_t tiles, int64_t ct) { return cb::stats_error2(tiles, ct); }
 double apply_cost(int64_t sub, int64_t per, int64_t groups, int64_t n_cu, int64_t resident, double rate) {
     return cb::apply_cost(sub, per, groups, n_cu, resident, rate);
@@ -39,6 +40,7 @@ def rules(tmp_path_factory):
     ip = ctypes.POINTER(ctypes.c_int)
     lib.stats_chunks.argtypes = [i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_double, ip, ip]
     lib.even_chunks.argtypes = [i64, ctypes.c_int, ctypes.c_int, ip, ip]
+    lib.most_chunks.argtypes = [i64, ctypes.c_int, ctypes.c_int]
     lib.stats_error2.argtypes, lib.stats_error2.restype = [i64, i64], ctypes.c_double
     return lib
 
@@ -49,20 +51,21 @@ def _chunks(f, *args):
     return nc.value, ct.value
 
 
-# Chunks of the moments: they cover the tiles, an fp32 sum runs over at most 2048 tiles and its error is at most that of
-# eight units per compute unit.
+# Chunks of the moments: they cover the tiles, an fp32 sum runs over at most 2048 tiles, its error is at most that of
+# eight units per compute unit, and a plan's workspace holds them for every call of up to its tiles.
 @pytest.mark.parametrize("unit_tiles", [5.3, 10.0, 35.3])
 @pytest.mark.parametrize("items", [1, 2, 6, 64, 76, 160, 161, 320, 512, 640, 2049, 5120])
 def test_stats_chunks_hold_their_bounds(rules, items, unit_tiles):
     for limit in [1, 31, 33, 500, 1030, 6400, 38936, 70000]:
+        most = rules.most_chunks(limit, items, 256)
         sizes = sorted({t for k in range(1, 60) for t in (limit * k // 59, limit // k)} | {1, limit}) if limit > 600 else \
             range(1, limit + 1)
         for tiles in sizes:
             if tiles < 1:
                 continue
-            nc, ct = _chunks(rules.stats_chunks, tiles, items, 256, 0, unit_tiles)
+            nc, ct = _chunks(rules.stats_chunks, tiles, items, 256, most, unit_tiles)
             n0, ct0 = _chunks(rules.even_chunks, tiles, items, 256)
-            assert 1 <= nc and (nc - 1) * ct < tiles <= nc * ct and ct <= 2048, (tiles, limit, nc, ct)
+            assert 1 <= nc <= most and (nc - 1) * ct < tiles <= nc * ct and ct <= 2048, (tiles, limit, nc, ct)
             assert rules.stats_error2(tiles, ct) <= rules.stats_error2(tiles, ct0), (tiles, limit, nc, ct, ct0)
 
 
