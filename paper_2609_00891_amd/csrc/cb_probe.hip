@@ -17,10 +17,12 @@
 // wave.  W is staged in LDS (every wave reads all of it); each element of A and B
 // is read once, from global memory, A a group of K steps ahead.  The traces and
 // TSS are summed in fp64 over the workgroup in a fixed order.
-// Bound: HBM, 196 KB per map at d_s = d_t = 128 (the fp32 products take 7 us of
-// a compute unit per map and overlap with the other map it holds).  Measured,
-// 10,240 maps of 128 and 128: 6.70 ms with FMAs from LDS, a thread per half row,
-// and one thread summing TSS; now 0.60 ms.
+// Bound: HBM, 196 KB per map at d_s = d_t = 128, and near it the fp32 products, 7
+// us of a compute unit per map: with 270 registers a lane a SIMD holds one wave at
+// d_t = 128 (two at 96, three at 64), that is one map per compute unit, whose loads
+// overlap with its own products only.  Measured, 10,240 maps of 128 and 128: 6.70
+// ms with FMAs from LDS, a thread per half row, and one thread summing TSS; now
+// 0.60 ms.
 #include "cb_internal.h"
 
 namespace cb {

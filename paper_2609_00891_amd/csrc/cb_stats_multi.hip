@@ -141,8 +141,8 @@ __device__ __forceinline__ void dma_tile(const uint32_t (&voff)[NL], const void 
 // read-modify-writes all of G and C (9.7 GB for 1,024 maps at k = 8).  Measured
 // with FB = 2 and 8, a call of 256 rows 4.36 -> 2.80 ms, 2,048 rows 7.8 -> 6.85,
 // 10,240 rows 30.4 -> 29.7.
-template <int FB>
 __device__ __forceinline__ void flush_rows(const float *tr, int lane, int mode, float *dst, float *mir, int64_t ld) {
+    constexpr int FB = 8;
     const int jj = lane & 31;
 #pragma unroll 1
     for (int i0 = 0; i0 < 16; i0 += FB) {
@@ -336,7 +336,6 @@ __device__ __forceinline__ void multi_wave(const MultiArgs &a, const MultiTask &
     const int P = CENTER ? a.P - 1 : a.P;                    // leading dimension of G (or A)
     float *Gm = a.G + (int64_t)tk.map * P * P;
     float *Cm = a.C + (int64_t)tk.map * P * a.d_t;
-    constexpr int FB = 8;                                    // row pairs requested together (see flush_rows)
     auto flush = [&]() {
         const float ex = sumx + __shfl_xor(sumx, 32);         // lanes l and l + 32: the two token halves
         if constexpr (CENTER) {
@@ -367,7 +366,7 @@ __device__ __forceinline__ void multi_wave(const MultiArgs &a, const MultiTask &
             float *dst = is_y ? Cm + (int64_t)(32 * R) * a.d_t + 32 * win : Gm + (int64_t)(32 * R) * P + 32 * Cc;
             float *mir = Gm + (int64_t)(32 * Cc) * P + 32 * R;
             const int64_t ld = is_y ? a.d_t : P;
-            flush_rows<FB>(tr, lane, mode, dst, mir, ld);
+            flush_rows(tr, lane, mode, dst, mir, ld);
         }
         if constexpr (CENTER) {
             if (a.resid && own_x && lane < 32) {
