@@ -41,26 +41,27 @@ inline double stats_error2(int64_t tiles, int64_t ct) {
 // about ceil(units / compute units) rounds of a chunk's tiles plus a fixed part
 // (ring fill and drain, about 5 tiles' time), and every unit's partial is written
 // and read again, `unit_tiles` tiles' bytes.  The cheapest count is taken among
-// those whose sums are as precise as those of eight units per compute unit
-// (stats_error2), and no longer than 2048 tiles.  Many short chunks may grow and
-// stay as precise; long ones may not: 1,024 maps over one 2,048-token sequence
-// keep 4 chunks of 16 tiles (540 us a call, G 2.5e-7 from 64 bits; one chunk of 64
-// took 335 us and left 4.0e-7, and sums of 16 tiles that a chunk of 64 adds to its
-// partial in memory take 500: it is the partials' traffic).
+// eight units per compute unit and fewer, longer chunks (of at most 2048 tiles)
+// whose sums are surely no less precise: stats_error2, which leaves out what else
+// rounds, a quarter below.  Many short chunks may grow; long ones may not: 1,024
+// maps over 2,048-token sequences keep 4 chunks of 16 tiles a call (G and C of four
+// calls 1.2e-7 from 64 bits, 500 us a call; one chunk of 64 left 2.3e-7 and took
+// 335, and sums of 16 tiles that a chunk of 64 adds to its partial in memory take
+// 500 too: it is the partials' traffic).
 // Measured, one call, eight units per compute unit -> this rule, us: 128 maps of
 // 128 and 128, 4 x 2,048 tokens 380 -> 181 (32 chunks per item -> 8), about means
-// 417 -> 185; 4 maps of 64 and 64, 4 x 256 tokens 40 -> 17 (32 -> 16), about means
-// 53 -> 19; two maps of 128 and 128, 65,536 tokens 3,120 -> 113 (2,048 -> 171).
+// 417 -> 187; 4 maps of 64 and 64, 4 x 256 tokens 40 -> 17 (32 -> 16), about means
+// 53 -> 19; two maps of 128 and 128, 65,536 tokens 3,120 -> 116 (2,048 -> 171).
 inline void choose_stats_chunks(int64_t tiles, int n_items, int n_cu, int max_chunks, double unit_tiles, int *n_chunks,
                                 int *chunk_tiles) {
     choose_chunks(tiles, n_items, n_cu, max_chunks, n_chunks, chunk_tiles);
-    const int64_t most = std::min<int64_t>({tiles, (int64_t)*n_chunks + *n_chunks / 8, max_chunks > 0 ? max_chunks : tiles});
-    const double limit = stats_error2(tiles, *chunk_tiles);
+    const int64_t most = *n_chunks, even = *chunk_tiles;
+    const double limit = 0.75 * stats_error2(tiles, even);
     double best = -1.0;
     for (int64_t nc = 1, ct = tiles, next; ct > 0 && nc <= most; nc = next) {
         ct = (tiles + nc - 1) / nc;
         next = ct > 1 ? (tiles + ct - 2) / (ct - 1) : most + 1;     // the first count with shorter chunks
-        if (ct > 2048 || stats_error2(tiles, ct) > limit) continue;
+        if (ct != even && (ct > 2048 || stats_error2(tiles, ct) > limit)) continue;
         const int64_t units = nc * n_items;
         const double cost = (double)((units + n_cu - 1) / n_cu) * (double)(ct + 5) + (double)units * unit_tiles / n_cu;
         if (best >= 0.0 && cost >= best) continue;
@@ -71,12 +72,11 @@ inline void choose_stats_chunks(int64_t tiles, int n_items, int n_cu, int max_ch
 }
 
 // The most chunks that choose_stats_chunks takes for any call of up to `tiles`
-// tiles (its count grows with the tiles, but for rounding).  Calls of many short
+// tiles: at most choose_chunks's, whose count before rounding grows with them.  Calls of many short
 // sequences can have more tiles than the plan's tokens fill; they are held to it.
 inline int32_t most_stats_chunks(int64_t tiles, int n_items, int n_cu) {
     const int64_t per_cu8 = (8LL * n_cu + n_items - 1) / n_items;
-    const int64_t nc = std::min(tiles, std::max(per_cu8, (tiles + 2047) / 2048));
-    return (int32_t)std::min(tiles, nc + nc / 8);
+    return (int32_t)std::min(tiles, std::max(per_cu8, (tiles + 2047) / 2048));
 }
 
 // Token tiles of the single-layer application, in 32-token sub-blocks: a

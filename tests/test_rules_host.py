@@ -51,8 +51,8 @@ def _chunks(f, *args):
     return nc.value, ct.value
 
 
-# Chunks of the moments: they cover the tiles, an fp32 sum runs over at most 2048 tiles, its error is at most that of
-# eight units per compute unit, and a plan's workspace holds them for every call of up to its tiles.
+# Chunks of the moments: they cover the tiles, an fp32 sum runs over at most 2048 tiles, chunks other than eight units per
+# compute unit are longer and leave at most three quarters of their squared error, and a plan's workspace holds them for every call of up to its tiles.
 @pytest.mark.parametrize("unit_tiles", [5.3, 10.0, 35.3])
 @pytest.mark.parametrize("items", [1, 2, 6, 64, 76, 160, 161, 320, 512, 640, 2049, 5120])
 def test_stats_chunks_hold_their_bounds(rules, items, unit_tiles):
@@ -66,7 +66,8 @@ def test_stats_chunks_hold_their_bounds(rules, items, unit_tiles):
             nc, ct = _chunks(rules.stats_chunks, tiles, items, 256, most, unit_tiles)
             n0, ct0 = _chunks(rules.even_chunks, tiles, items, 256)
             assert 1 <= nc <= most and (nc - 1) * ct < tiles <= nc * ct and ct <= 2048, (tiles, limit, nc, ct)
-            assert rules.stats_error2(tiles, ct) <= rules.stats_error2(tiles, ct0), (tiles, limit, nc, ct, ct0)
+            assert ct >= ct0 and (ct == ct0 or rules.stats_error2(tiles, ct) <= 0.75 * rules.stats_error2(tiles, ct0)), \
+                (tiles, limit, nc, ct, ct0)
 
 
 # Application tiles: the chosen one costs at most 10% more than the best of all, and at most 5% more than tiles of at least
