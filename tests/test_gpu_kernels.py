@@ -354,3 +354,25 @@ def test_wide_solve_many_centered(cb, dx):
     for m in range(2):
         assert bool((maps[m::2] == maps[m]).all())
         assert _relF(maps[m].double().cpu().numpy(), W[m]) < 1e-6
+
+
+# How long an fp32 sum runs: whole numbers whose sums are exact in fp32 over 16 tiles (below 2^24) but not over 64 (4e7).
+# 512 items and 64 tiles are 4 chunks of 16 tiles, so only three additions of chunks round: by at most half of 2, 2 and 4.
+def test_stats_sums_stay_short(cb):
+    L, Ls, H, d, T = 64, 4, 8, 64, 2048
+    rows = [(l, h, z, l % Ls, h, 0) for l in range(L) for z in range(2) for h in range(H)]
+    names = ("tgt_layer", "tgt_head", "kv", "src_layer", "src_head", "weight_row")
+    hm = {k: np.asarray(v, dtype=np.int32) for k, v in zip(names, zip(*rows))}
+    g = torch.Generator(device="cuda").manual_seed(3)
+    src = torch.randint(64, 201, (Ls, 2, 1, H, T, d), generator=g, device="cuda").bfloat16()
+    tgt = torch.randint(64, 201, (L, 2, 1, H, T, d), generator=g, device="cuda").bfloat16()
+    w = torch.ones((1, T), device="cuda")
+    plan = cb.cb_plan_create(hm, src, tgt, T)
+    G, C = torch.zeros((len(rows), d + 1, d + 1), device="cuda"), torch.zeros((len(rows), d + 1, d), device="cuda")
+    cb.cb_stats_accumulate(plan, src, tgt, w, G, C)
+    for m in range(0, len(rows), 37):
+        l, h, z, s, _, _ = rows[m]
+        x = torch.cat([src[s, z, 0, h].double(), torch.ones((T, 1), dtype=torch.float64, device="cuda")], dim=1)
+        y = tgt[l, z, 0, h].double()
+        assert 2 ** 25 < float((x.t() @ x)[0, 0]) < 2 ** 26
+        assert float((G[m].double() - x.t() @ x).abs().max()) <= 4 and float((C[m].double() - x.t() @ y).abs().max()) <= 4
