@@ -500,12 +500,6 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
         wait_vm_tied<0>(tB);
         turn_tile(tA, 0);
         turn_tile(tB, 1);
-        issue(cur, 2);
-        tab_load(tA, cur);
-        tile_next(cur);
-        issue(cur, 3);
-        tab_load(tB, cur);
-        tile_next(cur);                                      // ends at tile 4, the first one the loop copies
     } else {
 #pragma unroll
         for (int t = 0; t < K::NST; ++t) {
@@ -513,6 +507,18 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
             tile_next(cur);                                  // ends at tile 4, the first one the loop copies
         }
     }
+    // Rotary form: tiles 2 and 3 and their table entries.  Called on each of the two paths below and not before they
+    // part: where entries in flight reach two uses the compiler moves one pair of register sets, before they land.
+    auto fill_ring = [&]() __attribute__((always_inline)) {
+        if constexpr (RS != 0) {
+            issue(cur, 2);
+            tab_load(tA, cur);
+            tile_next(cur);
+            issue(cur, 3);
+            tab_load(tB, cur);
+            tile_next(cur);                                  // ends at tile 4, the first one the loop copies
+        }
+    };
     // In iteration t, after the copies of tile t + 4: tile t + 2 is turned with
     // its table entries (register set of its parity), whose set then receives
     // the entries of tile t + 4.  Only tile t + 3 and its entries and tile
@@ -525,10 +531,22 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
         }
     };
 
+    // After the loop: the trailing copies, and the last table entries, whose registers are taken until they have landed
+    // (no one reads them; without the names the compiler forms the stores' addresses in them before the wait).
+    auto drain = [&]() __attribute__((always_inline)) {
+        if constexpr (RS != 0) {
+            wait_vm_tied<0>(tA);
+            wait_vm_tied<0>(tB);
+        } else {
+            wait_vm<0>();
+        }
+    };
+
     if (slot >= c.n_slots) {
         // A wave without a map (single-map item) only helps with the copies; it
         // meets the same barriers as the computing waves below (one before the
         // loop, one per tile of the loop's even trip count).
+        fill_ring();
         wait_tiles(3);
         lds_barrier();
         for (int t = 0; t < ((c.n_tiles + 1) & ~1); t += 2) {
@@ -545,7 +563,7 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
             tile_next(cur);
             turn_ahead(tB, t + 1, q);
         }
-        wait_vm<0>();
+        drain();
         return;
     }
     // LDS offsets of this slot's tensors inside a stage
@@ -785,6 +803,7 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
         pin(f2);
         interleave();
     };
+    fill_ring();
     wait_tiles(3);                                           // tile 0 has landed
     lds_barrier();
     Ops a0, a1, b0, b1;
@@ -796,7 +815,7 @@ __device__ __forceinline__ void stats_wave(const StatsArgs &a, const StatsCtx c,
         iteration(t, a0, a1, fa, b0, b1, fb, tA);
         iteration(t + 1, b0, b1, fb, a0, a1, fa, tB);
     }
-    wait_vm<0>();                                            // drain the trailing copies before leaving
+    drain();
 
     float *P = a.partials + ((int64_t)c.unit * 2 + slot) * K::SLOT;
     constexpr int gbase = PR == 0 ? 0 : Own<K::RB, 0>::NG;

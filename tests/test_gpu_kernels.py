@@ -376,3 +376,33 @@ def test_stats_sums_stay_short(cb):
         y = tgt[l, z, 0, h].double()
         assert 2 ** 25 < float((x.t() @ x)[0, 0]) < 2 ** 26
         assert float((G[m].double() - x.t() @ x).abs().max()) <= 4 and float((C[m].double() - x.t() @ y).abs().max()) <= 4
+
+
+# Rotary statistics of plans with an item of a single map, whose other waves only copy and turn: chunks of several tiles,
+# whole and ragged ones.  The products are bit for bit those of turned copies (the bias sums may round differently).
+@pytest.mark.parametrize("maps", [1, 3])
+@pytest.mark.parametrize("d,style,T", [(128, 0, 2048), (128, 1, 2090), (64, 0, 2090), (64, 1, 2048)])
+def test_stats_rope_single_map_items(cb, d, style, T, maps):
+    rows = [(0, 0, 0, 0, 0, 0), (1, 0, 1, 1, 0, 0), (2, 0, 0, 2, 0, 0)][:maps]
+    names = ("tgt_layer", "tgt_head", "kv", "src_layer", "src_head", "weight_row")
+    hm = {k: np.asarray(v, dtype=np.int32) for k, v in zip(names, zip(*rows))}
+    g = torch.Generator(device="cuda").manual_seed(T + style)
+    src = torch.randn((3, 2, 6, 1, T, d), generator=g, device="cuda").bfloat16()
+    tgt = torch.randn((3, 2, 6, 1, T, d), generator=g, device="cuda").bfloat16()
+    w = torch.rand((1, 6 * T), generator=g, device="cuda")
+    tabs = [torch.empty((T + 7, d // 2, 2), device="cuda") for _ in range(2)]
+    for t, theta in zip(tabs, (1e4, 1e6)):
+        cb.cb_rope_table(theta, d, T + 7, t)
+    plan = cb.cb_plan_create(hm, src, tgt, 6 * T)
+    out = []
+    for fused in (True, False):
+        G, C = torch.zeros((maps, d + 1, d + 1), device="cuda"), torch.zeros((maps, d + 1, d), device="cuda")
+        if fused:
+            cb.cb_stats_accumulate_rope(plan, src, tgt, w, G, C, *(cb.rope_spec(t, style, 7) for t in tabs))
+        else:
+            turned = [x.clone() for x in (src, tgt)]
+            for x, y, t in zip((src, tgt), turned, tabs):
+                cb.cb_rope(x, y, t, style, True, 7)
+            cb.cb_stats_accumulate(plan, *turned, w, G, C)
+        out.append((G[:, :d, :d], C[:, :d]))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
