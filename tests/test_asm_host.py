@@ -1,4 +1,4 @@
-"""Host check (no GPU) of the compiled rotary statistics kernels: registers that inline-assembly loads are still
+"""Host analysis (no GPU) of the compiled rotary statistics kernels: registers that inline-assembly loads are still
 filling are left alone until a wait has covered them.
 
 The compiler takes the output of an inline load as written at once. It may copy such a register, or use it for
@@ -80,7 +80,7 @@ def touched_in_flight(body):
     return loads, sorted(bad)
 
 
-def test_checker_sees_copies_and_reuse():
+def test_analysis_sees_copies_and_reuse():
     asm = "\n".join(["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[2:5], v[8:9], off", "\t;;#ASMEND", "\t%s",
                      "\tglobal_store_dword v[10:11], v12, off", "\ts_waitcnt vmcnt(%d)", "\tv_mul_f32_e32 v2, v3, v4",
                      "\ts_endpgm"])
